@@ -64,11 +64,40 @@ __device__ inline void load_q_tile(uint4 (&q)[NKK], const uint16_t* __restrict__
 // every split of the capacity).  Items are numbered sequence-major, then KV
 // head, then split.  Each wave computes these wave-uniform values on its own
 // (lanes over sequences), so nothing is shared or cleared between launches.
-__device__ inline long long wave_sum_ll(long long v) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+//
+// Every workgroup of both launches waits for these values before its first
+// load, so they are kept short: 32-bit sums and scans through DPP lane moves
+// (no LDS permutes), and a bracket from float arithmetic (64-bit divisions
+// and shuffled 64-bit sums here took 3-5 us of each launch).
+// A lane move: lane l receives v of the lane that CTRL names, 0 where there
+// is none (or where ROWS masks its row of 16 out).
+template <int CTRL, int ROWS>
+__device__ inline int dpp_move(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, true);
+}
+// inclusive prefix sums over the wave's lanes (all 64 active)
+__device__ inline int wave_scan(int v) {
+  v += dpp_move<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8: prefix within each row of 16
+  v += dpp_move<0x112, 0xF>(v);
+  v += dpp_move<0x114, 0xF>(v);
+  v += dpp_move<0x118, 0xF>(v);
+  v += dpp_move<0x142, 0xA>(v);  // row_bcast 15: rows 1 and 3 add the row before
+  v += dpp_move<0x143, 0xC>(v);  // row_bcast 31: rows 2 and 3 add the first half
   return v;
 }
+__device__ inline int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), 63); }
+__device__ inline float wave_sum(float v) {
+  auto add = [](float a, int b) { return a + __int_as_float(b); };
+  v = add(v, dpp_move<0x111, 0xF>(__float_as_int(v)));
+  v = add(v, dpp_move<0x112, 0xF>(__float_as_int(v)));
+  v = add(v, dpp_move<0x114, 0xF>(__float_as_int(v)));
+  v = add(v, dpp_move<0x118, 0xF>(__float_as_int(v)));
+  v = add(v, dpp_move<0x142, 0xA>(__float_as_int(v)));
+  v = add(v, dpp_move<0x143, 0xC>(__float_as_int(v)));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+__device__ inline int splits_of(int L, int S) { return (int)(((uint32_t)L + (uint32_t)S - 1u) / (uint32_t)S); }
 
 // The clamped lengths of the sequences b = lane, lane + 64, ...: the first
 // held in a register (every sequence of a batch of up to 64), the rest
@@ -89,35 +118,43 @@ struct LaneLens {
   }
 };
 
-// (sequence, KV head, split) items of split length S
-__device__ inline long long fa_items_of(const LaneLens& ll, int Hkv, int S) {
-  long long n = 0;
-  ll.for_each([&](int, int L) { n += (L + S - 1) / S; });
-  return wave_sum_ll(n) * Hkv;
+// (sequence, KV head, split) items of split length S; S keeps them within
+// about n_items + B Hkv (the search's bracket), so 32 bits hold them
+__device__ inline int fa_items_of(const LaneLens& ll, int Hkv, int S) {
+  int n = 0;
+  ll.for_each([&](int, int L) { n += splits_of(L, S); });
+  return wave_sum(n) * Hkv;
 }
 
 __device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPlan& sp) {
   if (sp.fixed > 0) return sp.fixed;
-  long long tot = 0;
-  ll.for_each([&](int, int L) { tot += L; });
-  tot = wave_sum_ll(tot) * Hkv;  // token rows over every (sequence, KV head)
-  const long long units = (long long)ll.B * Hkv;
-  const long long al = sp.align;
+  float tot = 0.f;
+  ll.for_each([&](int, int L) { tot += (float)L; });
+  tot = wave_sum(tot) * (float)Hkv;  // token rows over every (sequence, KV head)
+  const int units = ll.B * Hkv;
+  const float al = (float)sp.align;
   // items(S) >= tot / S, so S >= tot / n_items; items(S) <= tot / S + units,
   // so S = tot / (n_items - units) fits (with n_items > units), as does any
-  // S of at least the capacity (the host makes n_items >= units)
-  const long long cap_u = (ll.max_len + al - 1) / al;
-  long long lo = max((sp.min_split + al - 1) / al, (tot + sp.n_items * al - 1) / (sp.n_items * al));
-  long long hi = sp.n_items > units ? (tot + (sp.n_items - units) * al - 1) / ((sp.n_items - units) * al) : cap_u;
-  hi = max(min(hi, cap_u), lo);  // items(lo) <= items(hi) when hi is raised to lo
-  while (lo < hi) {  // items(S) falls as S grows: the smallest S that fits
-    const long long mid = (lo + hi) / 2;
-    if (fa_items_of(ll, Hkv, (int)(mid * al)) <= sp.n_items)
+  // S of at least the capacity (the host makes n_items >= units).  Both ends
+  // of the bracket are moved out by more than the float sums' error: items(S)
+  // falls as S grows, so the smallest S that fits is the same.
+  const int cap_u = (ll.max_len + sp.align - 1) / sp.align;
+  const int min_u = (sp.min_split + sp.align - 1) / sp.align;
+  const float n = (float)sp.n_items;
+  int lo = max(min_u, (int)(tot * (0.9999f / (n * al))));
+  int hi = cap_u;
+  if (sp.n_items > units) hi = min(cap_u, (int)fminf(tot * (1.0001f / ((n - (float)units) * al)), 1e9f) + 1);
+  hi = max(hi, lo);  // items(lo) <= items(hi) when hi is raised to lo
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  hi = __builtin_amdgcn_readfirstlane(hi);
+  while (lo < hi) {
+    const int mid = (lo + hi) / 2;
+    if (fa_items_of(ll, Hkv, mid * sp.align) <= sp.n_items)
       hi = mid;
     else
       lo = mid + 1;
   }
-  return __builtin_amdgcn_readfirstlane((int)(hi * al));
+  return hi * sp.align;
 }
 
 // The (sequence, KV head, split) of item `item` with split length S; false
@@ -128,39 +165,33 @@ __device__ inline bool fa_locate(const LaneLens& ll, int Hkv, int S, int item, i
   for (int b0 = 0; b0 < ll.B; b0 += 64) {
     const int bb = b0 + lane;
     const int L = b0 == 0 ? ll.l0 : (bb < ll.B ? clamp_len(ll.len, bb, ll.max_len) : 0);
-    const int nb = (L + S - 1) / S;
-    int incl = nb * Hkv;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int y = __shfl_up(incl, o);
-      if (lane >= o) incl += y;
-    }
+    const int nb = splits_of(L, S);
+    const int incl = wave_scan(nb * Hkv);
     const unsigned long long hit = __ballot(incl > rem);
     if (hit) {
       const int l = __ffsll((long long)hit) - 1;
-      const int n = __shfl(nb, l);
-      const int r = rem - (__shfl(incl, l) - n * Hkv);  // item within sequence b0 + l
-      b = __builtin_amdgcn_readfirstlane(b0 + l);
-      g = __builtin_amdgcn_readfirstlane(r / n);
-      split = __builtin_amdgcn_readfirstlane(r % n);
+      const int n = __builtin_amdgcn_readlane(nb, l);
+      const int r = rem - (__builtin_amdgcn_readlane(incl, l) - n * Hkv);  // item within sequence b0 + l
+      b = b0 + l;
+      g = r / n;
+      split = r % n;
       return true;
     }
-    rem -= __shfl(incl, 63);
+    rem -= __builtin_amdgcn_readlane(incl, 63);
   }
   return false;
 }
 
 // First item of (sequence b, KV head g) with split length S.
 __device__ inline int fa_first_item(const LaneLens& ll, int Hkv, int S, int b, int g) {
-  long long n = 0;
+  int n = 0;
   int nb = 0;  // splits of sequence b (on the lane holding it)
   ll.for_each([&](int bb, int L) {
-    if (bb < b) n += (L + S - 1) / S;
-    if (bb == b) nb = (L + S - 1) / S;
+    const int k = splits_of(L, S);
+    if (bb < b) n += k;
+    if (bb == b) nb = k;
   });
-  n = wave_sum_ll(n) * Hkv;
-  nb = __shfl(nb, b & 63);  // lane b % 64 holds sequence b
-  return (int)n + g * nb;
+  return wave_sum(n) * Hkv + g * __builtin_amdgcn_readlane(nb, b & 63);  // lane b % 64 holds sequence b
 }
 
 // ============================================================================ full attention

@@ -46,8 +46,9 @@
  * Planner overrides (environment, read on every call; for tests and tuning,
  * invalid values fall back to the planner's choice): HS2_FA_VARIANT
  * (full-attention kernel shape), HS2_FA_SPLIT / HS2_POOL_SPLIT /
- * HS2_SA_SPLIT (tokens or slots per workgroup), HS2_FA_ROUNDS (workgroup
- * rounds the full-attention splits are sized for), HS2_POOL_FROM_K=1
+ * HS2_SA_SPLIT (tokens or slots per workgroup), HS2_SA_UNIT (sparse layers: 0
+ * the split kernel, 4 or 8 the waves of the one-workgroup-per-row kernel),
+ * HS2_FA_ROUNDS (workgroup rounds the full-attention splits are sized for), HS2_POOL_FROM_K=1
  * (recompute the scores from K even where the stored logits would serve),
  * HS2_FA_CACHE_POLICY (0: every full-attention load cacheable, 1: V rows
  * non-temporal, 2: K and V non-temporal, 3: V and the leading K rows of

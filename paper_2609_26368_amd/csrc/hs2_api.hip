@@ -87,6 +87,7 @@ struct Plan {
 
 struct SaPlan {
   int RT, TG, split, nsplit, n_slots;
+  int unit_waves;  // waves of the sa_unit kernel, 0: the split kernel
   size_t off_part_o, off_part_ml, bytes;
 };
 
@@ -295,8 +296,30 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   s.nsplit = (int)cdiv(n_slots, split);
   const int64_t prow = 16 * s.RT;
   size_t cur = 0;
-  s.off_part_o = carve(cur, sizeof(float) * p.rows * s.nsplit * s.TG * prow * p.D);
-  s.off_part_ml = carve(cur, sizeof(float) * p.rows * s.nsplit * s.TG * prow * 4);
+  // The sa_unit kernel: from 128 workgroups of a 16-head tile of a row on
+  // (they keep half the chip's gathers busy by themselves) always, its rows
+  // cut into the fewest splits that its LDS holds; with fewer, only rows that
+  // one workgroup finishes before the split kernel and its merge would
+  // (measured crossings at 2-32 workgroups: 900-1150 slots at head dim 128,
+  // 500-650 at 256).  Eight waves while there are not two workgroups per
+  // compute unit, four (two workgroups per unit) from then on.  The rule
+  // takes no device figures and no cache format.  HS2_SA_SPLIT keeps the
+  // split kernel, HS2_SA_UNIT = 0, 4 or 8 chooses.
+  const int64_t wgs = p.rows * cdiv(p.G, 16);
+  const int alone = p.D == 256 ? 512 : 896;
+  s.unit_waves = env_int("HS2_SA_SPLIT", 0) > 0 || (wgs < 128 && n_slots > alone) ? 0 : wgs >= 384 ? 4 : 8;
+  const int forced = env_int("HS2_SA_UNIT", -1);
+  if (forced == 0 || forced == 4 || forced == 8) s.unit_waves = forced;
+  // the workspace is sized for the split kernel, which needs more partials
+  const int split_nsplit = s.nsplit;
+  if (wgs * cdiv(n_slots, kSaUnitSlots) > (1 << 22)) s.unit_waves = 0;  // its grid is one-dimensional
+  if (s.unit_waves) {
+    s.nsplit = (int)cdiv(n_slots, kSaUnitSlots);
+    s.split = (int)round_up(cdiv(n_slots, s.nsplit), 16);
+  }
+  const int64_t parts = p.rows * std::max(s.nsplit, split_nsplit) * s.TG * prow;
+  s.off_part_o = carve(cur, sizeof(float) * parts * p.D);
+  s.off_part_ml = carve(cur, sizeof(float) * parts * 4);
   s.bytes = (size_t)round_up((int64_t)cur, kAlign);
 }
 
@@ -755,7 +778,17 @@ hs2_status sparse_impl(const hs2_dims* dims, const uint16_t* q, const void* K, c
   a.n_slots = n_slots;
   a.split_slots = sp.split;
   a.n_split = sp.nsplit;
-  HS2_TRY_LAUNCH(KK_SA, s, launch_sa_split(a, sp.RT, s));
+  a.part_rows = 16 * sp.RT;
+  a.out = out;
+  a.sink = sink;
+  a.gate = gate;
+  a.v_scale = v_scale;
+  if (sp.unit_waves) {
+    HS2_TRY_LAUNCH(KK_SA, s, launch_sa_unit(a, sp.unit_waves, s));
+    if (sp.nsplit == 1) return HS2_OK;
+  } else {
+    HS2_TRY_LAUNCH(KK_SA, s, launch_sa_split(a, sp.RT, s));
+  }
 
   CombineArgs ca{};
   ca.part_o = a.part_o;

@@ -566,6 +566,35 @@ __global__ __launch_bounds__(64 * NWV * TGW) void k_fa_ring(FaArgs a) {
 }
 
 // ============================================================================ combine
+// Four output values (columns 4 dq ..) of row orow: the merged O over Z,
+// times the cache's output scale, times sigmoid of the four bf16 gate logits,
+// rounded to bf16.
+template <int HDIM>
+__device__ inline void store_out4(float4 o, float Z, float v_scale, const uint2* gate, uint16_t* out, int64_t orow,
+                                  int dq) {
+  const float inv = (Z > 0.f ? 1.f / Z : 0.f) * v_scale;
+  o.x *= inv;
+  o.y *= inv;
+  o.z *= inv;
+  o.w *= inv;
+  if (gate) {
+    const uint2 gb = *gate;
+    const float gv[4] = {bf16_bits_to_f32(gb.x & 0xFFFFu), bf16_bits_to_f32(gb.x >> 16), bf16_bits_to_f32(gb.y & 0xFFFFu),
+                         bf16_bits_to_f32(gb.y >> 16)};
+    float gsig[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) gsig[j] = 1.f / (1.f + fast_exp2(-gv[j] * 1.4426950408889634f));
+    o.x *= gsig[0];
+    o.y *= gsig[1];
+    o.z *= gsig[2];
+    o.w *= gsig[3];
+  }
+  uint2 packed;
+  packed.x = f32_to_bf16_bits(o.x) | (f32_to_bf16_bits(o.y) << 16);
+  packed.y = f32_to_bf16_bits(o.z) | (f32_to_bf16_bits(o.w) << 16);
+  *(uint2*)(out + orow * HDIM + 4 * dq) = packed;
+}
+
 // grid (rows_per_unit, units), 256 threads = 256 / NQ slot groups x NQ =
 // HDIM / 4 column quads.
 // FA: unit = (b, g), row r = c * Gp + h; slots valid = ceil(Lv / split) * TG.
@@ -658,27 +687,8 @@ __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
     o.w += s_o[j][dq].w;
   }
   if (sink2 != -INFINITY) Z += fast_exp2(sink2 - M);
-  const float inv = (Z > 0.f ? 1.f / Z : 0.f) * (a.v_scale ? a.v_scale[g] : 1.f);
-  o.x *= inv;
-  o.y *= inv;
-  o.z *= inv;
-  o.w *= inv;
-  if (a.gate) {  // out *= sigmoid(gate), elementwise
-    const uint2 gb = *(const uint2*)(a.gate + orow * HDIM + 4 * dq);
-    const float gv[4] = {bf16_bits_to_f32(gb.x & 0xFFFFu), bf16_bits_to_f32(gb.x >> 16), bf16_bits_to_f32(gb.y & 0xFFFFu),
-                         bf16_bits_to_f32(gb.y >> 16)};
-    float gsig[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) gsig[j] = 1.f / (1.f + fast_exp2(-gv[j] * 1.4426950408889634f));
-    o.x *= gsig[0];
-    o.y *= gsig[1];
-    o.z *= gsig[2];
-    o.w *= gsig[3];
-  }
-  uint2 packed;
-  packed.x = f32_to_bf16_bits(o.x) | (f32_to_bf16_bits(o.y) << 16);
-  packed.y = f32_to_bf16_bits(o.z) | (f32_to_bf16_bits(o.w) << 16);
-  *(uint2*)(a.out + orow * HDIM + 4 * dq) = packed;
+  store_out4<HDIM>(o, Z, a.v_scale ? a.v_scale[g] : 1.f, a.gate ? (const uint2*)(a.gate + orow * HDIM) + dq : nullptr,
+                   a.out, orow, dq);
   if (dq == 0) {
     if (a.stats_log2) {
       a.stats_log2[orow * 2] = M;
@@ -1946,11 +1956,8 @@ __global__ __launch_bounds__(64 * NWV) void k_sa_ring(SaArgs a) {
   const int64_t stride_t = a.stride_t * ESZ;
   const float c2 = KV8 ? a.c2 * a.k_scale[g] : a.c2;
   const uint32_t ring = lds_addr(smem);
-  uint32_t vmask[NS];  // row-validity bits of each ring stage (wave-uniform)
-
-  auto issue = [&](int tile) {
+  auto issue = [&](int tile) __attribute__((always_inline)) {
     const uint32_t base = ring + (uint32_t)((tile % NS) * SB);
-    uint32_t mask = 0;
 #pragma unroll
     for (int u = 0; u < LPM; ++u) {
       const int n = wave * LPM + u;
@@ -1960,40 +1967,27 @@ __global__ __launch_bounds__(64 * NWV) void k_sa_ring(SaArgs a) {
                           (KV8 ? 16 * ((lane % CPR) ^ raw_swz<RB>(row)) : 16 * ((lane % CPR) ^ stage_swz(row)));
       dma16(Kbg + off, __builtin_amdgcn_readfirstlane(base + 1024 * n));
       dma16(Vbg + off, __builtin_amdgcn_readfirstlane(base + TW * RB + 1024 * n));
-      const uint64_t bal = __ballot(t >= 0);  // lanes CPR j .. hold row RPL n + j
-#pragma unroll
-      for (int j = 0; j < RPL; ++j) mask |= (uint32_t)((bal >> (CPR * j)) & 1ull) << (RPL * n + j);
     }
-    return mask;
   };
 
   WaveState<RPW, HDIM> st;
   st.init();
+  // One wave alone owns its ring: a stage is refilled as soon as it has been
+  // read, so all NS stages are in flight while the wave waits.  Several waves
+  // share it: a stage is refilled after the next tile's barrier.
+  constexpr int AHEAD = NWV == 1 ? NS : NS - 1;
 #pragma unroll
-  for (int i = 0; i < NS - 1; ++i)
-    if (i < ntiles) vmask[i] = issue(i);
+  for (int i = 0; i < AHEAD; ++i)
+    if (i < ntiles) issue(i);
   for (int i = 0; i < ntiles; ++i) {
-    wait_ring<2 * LPM>(min(NS - 2, ntiles - 1 - i));
-    if (NWV > 1) __syncthreads();
-    uint32_t m_i = 0;
-#pragma unroll
-    for (int k = 0; k < NS; ++k)
-      if (k == i % NS) m_i = vmask[k];
-    if (i + NS - 1 < ntiles) {
-      const uint32_t mnew = issue(i + NS - 1);
-#pragma unroll
-      for (int k = 0; k < NS; ++k)
-        if (k == (i + NS - 1) % NS) vmask[k] = mnew;
+    wait_ring<2 * LPM>(min(AHEAD - 1, ntiles - 1 - i));
+    if (NWV > 1) {
+      __syncthreads();
+      if (i + NS - 1 < ntiles) issue(i + NS - 1);
     }
     const unsigned char* stg = smem + (i % NS) * SB;
-    if (NWV > 1) {  // every wave's row bits
-      __shared__ uint32_t s_mask[NWV];
-      if (lane == 0) s_mask[wave] = m_i;
-      __syncthreads();
-      m_i = 0;
-#pragma unroll
-      for (int w = 0; w < NWV; ++w) m_i |= s_mask[w];
-    }
+    // the tile's row-validity bits, lanes TW .. repeating the rows
+    const uint32_t m_i = (uint32_t)__ballot(sidx[i * TW + lane % TW] >= 0);
     f32x4 S[NB][RPW];
 #pragma unroll
     for (int bi = 0; bi < NB; ++bi) {
@@ -2017,9 +2011,221 @@ __global__ __launch_bounds__(64 * NWV) void k_sa_ring(SaArgs a) {
       pv_tile_e4m3<RPW, NB, HDIM, RB>(st, pf, stg + TW * RB, lane);
     else
       pv_tile<RPW, NB, HDIM>(st, pf, stg + TW * SRB, lane);
+    if (NWV == 1) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stage has been read
+      asm volatile("" ::: "memory");
+      if (i + NS < ntiles) issue(i + NS);
+    }
   }
   const int64_t slot_base_row = (unit * a.n_split + split) * (16 * RT);
   store_partial<RPW>(st, a.part_o, a.part_ml, slot_base_row, rt0, lane);
+}
+
+// The same layer with one workgroup per (selection row, 16-head tile, split):
+// its NW waves take every NW-th tile of the split's slots through rings of
+// their own and meet in LDS, so a split of up to kSaUnitSlots slots leaves
+// one partial, and a row that is one split needs no merge launch: the
+// workgroup normalises and writes the output itself.  Bound by the chain of
+// memory latencies (indices, gathers, about 0.5 us per further tile and
+// wave) when there are few rows, by the gather rate when there are many.
+// Against the split kernel and its merge (head dim 128, bf16, us per layer):
+// 2 rows of 320 slots 11.0 -> 6.8, 128 rows of 640 16.0 -> 11.3, 256 rows of
+// 1152 39.4 -> 30.3, 512 rows of 640 41.8 -> 33.1; slower where few
+// workgroups hold long rows (4 rows of 2304: 10.0 -> 17.7), which
+// use_sa_unit leaves to the split kernel.
+template <int NW, bool KV8, int HDIM>
+struct SaUnit {
+  static constexpr int RB = KV8 ? HDIM : 2 * HDIM;  // bytes of a staged row
+  // both cache formats take the same tiles: the same cache values give the same bits
+  static constexpr int TW = 16;
+  static constexpr int SB = 2 * TW * RB;            // stage: K rows, V rows
+  static constexpr int NS = 16384 / SB;             // 16 KB of stages per wave
+  static constexpr int RING = NW * NS * SB;
+  static_assert(RING >= NW * 16 * HDIM * 4, "the waves' outputs meet in the rings' LDS");
+  // a wave's share of a split's slot indices: whole tiles
+  __host__ __device__ static constexpr int wave_slots(int split_slots) {
+    return ((split_slots + TW - 1) / TW + NW - 1) / NW * TW;
+  }
+  static size_t lds(int split_slots) { return (size_t)RING + sizeof(int32_t) * NW * wave_slots(split_slots); }
+};
+template <int NW, bool KV8, int HDIM>
+__global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
+  using U = SaUnit<NW, KV8, HDIM>;
+  constexpr int TW = U::TW, NS = U::NS, SB = U::SB, RB = U::RB;
+  constexpr int NKK = HDIM / 32;
+  constexpr int RPL = 1024 / RB;       // rows per 1 KB load
+  constexpr int CPR = RB / 16;         // 16-byte chunks per staged row
+  constexpr int LPM = TW * RB / 1024;  // 1 KB loads per matrix per stage
+  constexpr int NQ = HDIM / 4;         // column quads of the output
+  constexpr int EPT = 16 * NQ / (64 * NW);  // output quads per thread
+  static_assert(EPT >= 1 && EPT * 64 * NW == 16 * NQ, "whole output quads per thread");
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ float s_m[NW][16], s_l[NW][16], s_sink[16];
+
+  const int units = a.B * a.Hkv * a.C;
+  const int ht = (a.G + 15) / 16;  // 16-head tiles
+  // a row's head tiles and splits are `units` workgroups apart: with a
+  // multiple of 8 rows they run on one XCD and share its L2
+  const int unit = blockIdx.x % units;
+  const int h0 = 16 * ((blockIdx.x / units) % ht);
+  const int split = blockIdx.x / units / ht;
+  const int c = unit % a.C;
+  const int g = (unit / a.C) % a.Hkv;
+  const int b = unit / (a.C * a.Hkv);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int s_begin = split * a.split_slots;
+  const int nslots = min(a.n_slots - s_begin, a.split_slots);
+  const int all_tiles = (nslots + TW - 1) / TW;
+  const int ntiles = all_tiles > wave ? (all_tiles - wave + NW - 1) / NW : 0;  // tiles wave, wave + NW, ...
+  const int wave_slots = U::wave_slots(a.split_slots);
+  int32_t* sidx = (int32_t*)(smem + U::RING) + wave * wave_slots;
+  unsigned char* ring_p = smem + wave * NS * SB;
+  const uint32_t ring = lds_addr(ring_p);
+
+  // everything the layer reads besides the cache is loaded before the first
+  // wait: the launch is a chain of memory latencies
+  constexpr int IR = (U::wave_slots(kSaUnitSlots) + 63) / 64;
+  const int32_t* irow = a.idx + (int64_t)unit * a.idx_stride + s_begin;
+  int iv[IR];
+#pragma unroll
+  for (int k = 0; k < IR; ++k) {
+    const int e = 64 * k + lane;
+    const int slot = (wave + NW * (e / TW)) * TW + e % TW;
+    iv[k] = e < wave_slots && slot < nslots ? irow[slot] : -1;
+  }
+  uint4 q[1][NKK];
+  {
+    const int h = h0 + (lane & 15);
+    const uint16_t* p = a.q + (((int64_t)b * a.C + c) * a.Hq + g * a.G + (h < a.G ? h : 0)) * HDIM;
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      q[0][kk] = *(const uint4*)(p + q_koff(kk, lane));
+      if (h >= a.G) q[0][kk] = make_uint4(0, 0, 0, 0);
+    }
+  }
+  const bool whole = a.n_split == 1;  // this workgroup writes the output
+  const int64_t orow0 = ((int64_t)b * a.C + c) * a.Hq + (int64_t)g * a.G + h0;
+  uint2 gate[EPT];
+  float sink2 = -INFINITY;
+  if (whole) {
+    if (a.gate)
+#pragma unroll
+      for (int k = 0; k < EPT; ++k) {
+        const int e = threadIdx.x + 64 * NW * k, r = e / NQ;
+        if (h0 + r < a.G) gate[k] = *(const uint2*)(a.gate + (orow0 + r) * HDIM + 4 * (e % NQ));
+      }
+    if (a.sink && h0 + (lane & 15) < a.G) sink2 = a.sink[g * a.G + h0 + (lane & 15)] * 1.4426950408889634f;
+  }
+  const float v_scale = KV8 ? a.v_scale[g] : 1.f;
+  const int Lv = clamp_len(a.len, b, a.max_len);
+#pragma unroll
+  for (int k = 0; k < IR; ++k)
+    if (64 * k + lane < wave_slots) sidx[64 * k + lane] = (iv[k] >= 0 && iv[k] < Lv) ? iv[k] : -1;
+  constexpr int ESZ = KV8 ? 1 : 2;  // bytes per cache element
+  const int64_t kvoff = ((int64_t)b * a.stride_b + (int64_t)g * a.stride_h) * ESZ;
+  const unsigned char* Kbg = (const unsigned char*)a.K + kvoff;
+  const unsigned char* Vbg = (const unsigned char*)a.V + kvoff;
+  const int64_t stride_t = a.stride_t * ESZ;
+  const float c2 = KV8 ? a.c2 * a.k_scale[g] : a.c2;
+  __builtin_amdgcn_s_waitcnt(vmcnt_enc(0));
+  asm volatile("" ::: "memory");
+
+  auto issue = [&](int tile) __attribute__((always_inline)) {
+    const uint32_t base = ring + (uint32_t)((tile % NS) * SB);
+#pragma unroll
+    for (int u = 0; u < LPM; ++u) {
+      const int row = RPL * u + lane / CPR;
+      const int t = sidx[tile * TW + row];
+      const int64_t off = (int64_t)(t < 0 ? 0 : t) * stride_t +
+                          16 * ((lane % CPR) ^ (KV8 ? raw_swz<RB>(row) : stage_swz(row)));
+      dma16(Kbg + off, __builtin_amdgcn_readfirstlane(base + 1024 * u));
+      dma16(Vbg + off, __builtin_amdgcn_readfirstlane(base + TW * RB + 1024 * u));
+    }
+  };
+
+  WaveState<1, HDIM> st;
+  st.init();
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+    if (i < ntiles) issue(i);
+  for (int i = 0; i < ntiles; ++i) {
+    wait_ring<2 * LPM>(min(NS - 1, ntiles - 1 - i));
+    asm volatile("" ::: "memory");
+    const unsigned char* stg = ring_p + (i % NS) * SB;
+    // the tile's row-validity bits (lanes TW .. repeat the rows)
+    const uint32_t m_i = (uint32_t)__ballot(sidx[i * TW + lane % TW] >= 0);
+    f32x4 S[1][1];
+    if constexpr (KV8)
+      qk_block_e4m3<1, RB>(stg, 0, q, S[0], lane);
+    else
+      qk_block_swz<1>(stg, 0, q, S[0], lane);
+#pragma unroll
+    for (int ii = 0; ii < 4; ++ii) {
+      const int row = 4 * (lane >> 4) + ii;
+      S[0][0][ii] = ((m_i >> row) & 1u) ? S[0][0][ii] * c2 : -INFINITY;
+    }
+    PFrags<1, 1> pf;
+    online_softmax(st, S, pf, lane);
+    if constexpr (KV8)
+      pv_tile_e4m3<1, 1, HDIM, RB>(st, pf, stg + TW * RB, lane);
+    else
+      pv_tile<1, 1, HDIM>(st, pf, stg + TW * RB, lane);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the stage has been read
+    asm volatile("" ::: "memory");
+    if (i + NS < ntiles) issue(i + NS);  // refilled at once: every stage is in flight while the wave waits
+  }
+
+  // merge: (m, l) of every wave, then each wave's O scaled to the common
+  // maximum (the sink's logit takes part), summed over the waves
+  const float l_row = sum_xor32(sum_xor16(st.l[0]));
+  if (lane < 16) {
+    s_m[wave][lane] = st.m[0];
+    s_l[wave][lane] = l_row;
+    if (wave == 0) s_sink[lane] = sink2;
+  }
+  __syncthreads();  // and every ring is free
+  auto row_max = [&](int r) {
+    float M = s_sink[r];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][r]);
+    return M;
+  };
+  float* oL = (float*)smem;  // [NW][16][HDIM]
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 4 * (lane >> 4) + i;
+    if (h0 + r < a.G) {
+      const float M = row_max(r);
+      const float f = M == -INFINITY ? 0.f : fast_exp2(s_m[wave][r] - M);
+#pragma unroll
+      for (int nb = 0; nb < HDIM / 16; ++nb) oL[(wave * 16 + r) * HDIM + 16 * nb + (lane & 15)] = st.o[0][nb][i] * f;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int e = threadIdx.x + 64 * NW * k, r = e / NQ, dq = e % NQ;
+    if (h0 + r >= a.G) continue;
+    const float M = row_max(r);
+    float Z = M == -INFINITY ? 0.f : fast_exp2(s_sink[r] - M);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      Z += M == -INFINITY ? 0.f : s_l[w][r] * fast_exp2(s_m[w][r] - M);
+      const float4 x = *(const float4*)(oL + (w * 16 + r) * HDIM + 4 * dq);
+      o.x += x.x;
+      o.y += x.y;
+      o.z += x.z;
+      o.w += x.w;
+    }
+    if (whole) {
+      store_out4<HDIM>(o, Z, v_scale, a.gate ? &gate[k] : nullptr, a.out, orow0 + r, dq);
+    } else {
+      const int64_t prow = ((int64_t)unit * a.n_split + split) * a.part_rows + h0 + r;
+      *(float4*)(a.part_o + prow * HDIM + 4 * dq) = o;
+      if (dq == 0) *(float4*)(a.part_ml + prow * 4) = make_float4(M, Z, M, 0.f);
+    }
+  }
 }
 
 // ============================================================================ streaming-read probe
@@ -2369,6 +2575,7 @@ hipError_t launch_pool(const PoolArgs& a, int RT, hipStream_t s) {
 
 // sparse-attention ring kernels: (RT, waves) per head dim; 32-row stages x 2
 constexpr int SAR_TW = 32, SAR_NS = 2;
+#define HS2_SA_UNIT_SHAPES(X) X(4, 128) X(8, 128) X(4, 256) X(8, 256)  // waves, head dim
 #define HS2_SA_SHAPES(X) X(1, 1, 128) X(2, 1, 128) X(4, 2, 128) X(1, 1, 256) X(2, 2, 256) X(4, 4, 256)
 
 hipError_t set_pool_smem_limits() {
@@ -2386,6 +2593,11 @@ hipError_t set_pool_smem_limits() {
   HS2_POOL_CASES(HS2_POOL_ATTR)
 #undef HS2_POOL_ATTR
   allow((const void*)k_block_select);
+#define HS2_SA_UNIT_ATTR(nw, hd)                      \
+  allow((const void*)k_sa_unit<nw, false, hd>);       \
+  allow((const void*)k_sa_unit<nw, true, hd>);
+  HS2_SA_UNIT_SHAPES(HS2_SA_UNIT_ATTR)
+#undef HS2_SA_UNIT_ATTR
   if (e == hipSuccess)  // its static LDS is large: only the bitmap's own limit
     e = hipFuncSetAttribute((const void*)k_sel_finish<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)SEL_BM_LDS_MAX);
@@ -2473,6 +2685,22 @@ hipError_t launch_sa_split(const SaArgs& a, int RT, hipStream_t s) {
   }
   HS2_SA_SHAPES(HS2_SA_LAUNCH)
 #undef HS2_SA_LAUNCH
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_sa_unit(const SaArgs& a, int NW, hipStream_t s) {
+  if (a.split_slots > kSaUnitSlots) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(a.B * a.Hkv * a.C * ((a.G + 15) / 16) * a.n_split));
+#define HS2_SA_UNIT_LAUNCH(nw, hdim)                                                                      \
+  if (NW == nw && a.hd == hdim) {                                                                         \
+    if (a.k_scale)                                                                                        \
+      HS2_LAUNCH((k_sa_unit<nw, true, hdim>), grid, dim3(64 * nw), (SaUnit<nw, true, hdim>::lds(a.split_slots)), s, a);   \
+    else                                                                                                  \
+      HS2_LAUNCH((k_sa_unit<nw, false, hdim>), grid, dim3(64 * nw), (SaUnit<nw, false, hdim>::lds(a.split_slots)), s, a); \
+    return hipGetLastError();                                                                             \
+  }
+  HS2_SA_UNIT_SHAPES(HS2_SA_UNIT_LAUNCH)
+#undef HS2_SA_UNIT_LAUNCH
   return hipErrorInvalidValue;
 }
 

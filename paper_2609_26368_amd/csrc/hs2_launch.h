@@ -126,6 +126,13 @@ struct SaArgs {
   int n_slots, split_slots, n_split;
   const float* k_scale;  // [Hkv] for an E4M3 cache, else null
   int hd;                // head dim (128 or 256)
+  // launch_sa_unit: partial rows per split (n_split > 1), or with one split
+  // the output and what the merge would apply to it
+  int part_rows;
+  uint16_t* out;         // [B, C, Hq, D] bf16
+  const float* sink;     // [Hq] sink logits or null
+  const uint16_t* gate;  // [B, C, Hq, D] bf16 output gate logits or null
+  const float* v_scale;  // [Hkv] E4M3 cache: output scale of each KV head, or null
 };
 
 constexpr int kFaVariants = 9;             // full-attention kernel shapes (see HS2_RING_VARIANTS)
@@ -151,6 +158,11 @@ hipError_t launch_sel_hist(const SelArgs& a, int nchunks, hipStream_t s);
 hipError_t launch_select(const SelArgs& a, hipStream_t s);
 hipError_t launch_block_select(const BlockSelArgs& a, hipStream_t s);  // block sums + selection
 hipError_t launch_sa_split(const SaArgs& a, int RT, hipStream_t s);
+// sparse layer with one workgroup of NW (4 or 8) waves per (sequence, KV head,
+// query, 16-head tile, split of at most kSaUnitSlots slots); with one split it
+// writes the output, else one partial per split for launch_combine
+constexpr int kSaUnitSlots = 2304;
+hipError_t launch_sa_unit(const SaArgs& a, int NW, hipStream_t s);
 // streaming-read probe over n16 16-byte words (mode: 0 register loads, 1
 // non-temporal register loads, 2 direct-to-LDS loads, 3 non-temporal
 // direct-to-LDS loads); workgroup w stores a fold of its slice to sink[w]

@@ -102,14 +102,19 @@ def make_dims(batch, n_queries, n_q_heads, n_kv_heads, head_dim, max_len, kv_str
     return hs2_dims(batch, n_queries, n_q_heads, n_kv_heads, head_dim, max_len, *kv_strides, scale)
 
 
+# The calls below are a decode loop's inner calls: a launch takes the host 2-3
+# us, so the marshalling is kept to plain integers: with a ctypes object per
+# pointer and a Stream object per call it took 10.7 us of a full call and 7.8
+# of a sparse one, now 7.5 and 5.1 (a 32K decode step of 1 + 3 layers, bound
+# by the host: 81 -> 68 us).
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    if stream is None:  # torch's current stream on the current device
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _check(status: int):
@@ -121,7 +126,7 @@ def _check(status: int):
 def _expect(t, name, shape, dtypes, device):
     if t is None:
         raise ValueError(f"{name} is required")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
     if t.dtype not in dtypes:
         raise ValueError(f"{name}: dtype {t.dtype}, expected one of {dtypes}")
@@ -139,12 +144,12 @@ _FP8 = (torch.uint8, torch.float8_e4m3fn)
 
 def _check_kv(dims, K, V, device, fp8=False):
     dtypes, what = (_FP8, "E4M3 (uint8)") if fp8 else (_BF16, "bf16")
+    # largest element offset the kernels may touch must lie inside the tensor's storage
+    last = ((dims.batch - 1) * dims.kv_stride_b + (dims.n_kv_heads - 1) * dims.kv_stride_h
+            + (dims.max_len - 1) * dims.kv_stride_t + dims.head_dim)
     for name, t in (("K", K), ("V", V)):
         if t.dtype not in dtypes or t.device != device:
             raise ValueError(f"{name}: {what} tensor on {device} expected")
-        # largest element offset the kernels may touch must lie inside the tensor's storage
-        last = ((dims.batch - 1) * dims.kv_stride_b + (dims.n_kv_heads - 1) * dims.kv_stride_h
-                + (dims.max_len - 1) * dims.kv_stride_t + dims.head_dim)
         avail = t.untyped_storage().nbytes() // t.element_size() - t.storage_offset()
         if last > avail:
             raise ValueError(f"{name}: strides address {last} elements, storage holds {avail}")

@@ -326,9 +326,9 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 // ---------------------------------------------------------------- timing
-enum KernelKind { KK_FA = 0, KK_COMBINE, KK_POOL, KK_POOL_LOGITS, KK_SEL_INIT, KK_SEL_HIST, KK_SELECT,
+enum KernelKind { KK_FA = 0, KK_COMBINE, KK_POOL, KK_POOL_LOGITS, KK_SCORE_SELECT, KK_SEL_INIT, KK_SEL_HIST, KK_SELECT,
                   KK_BLOCK_SELECT, KK_SA, KK_SA_COMBINE, KK_COUNT };
-const char* kKindNames[KK_COUNT] = {"fa_split", "fa_combine", "pool_scores", "pool_logits", "sel_init", "sel_hist",
+const char* kKindNames[KK_COUNT] = {"fa_split", "fa_combine", "pool_scores", "pool_logits", "score_select", "sel_init", "sel_hist",
                                     "select", "block_select", "sa_split", "sa_combine"};
 constexpr int kMaxTimed = 16384;
 struct Timing {
@@ -597,11 +597,15 @@ hs2_status full_attn_impl(const hs2_dims* dims, const uint16_t* q, const void* K
   ca.tg = p.TG;
   ca.sp = p.fa_sp;
   ca.sa_mode = 0;
-  // the histogram and the per-row counters (contiguous) start at zero
   ca.v_scale = v_scale;
   ca.hd = p.D;
-  ca.clear = block ? nullptr : (uint4*)(ws + p.off_hist);
-  ca.n_clear = (int64_t)(p.off_state - p.off_hist + sizeof(int32_t) * p.rows * 8) / 16;
+  // short rows with stored logits: scores and selection in one launch
+  const bool fused = p.pool_logits && !block && score_select_serves(p.Lmax);
+  // the histogram (not the fused rows': theirs is in LDS) and the per-row
+  // counters (contiguous) start at zero
+  const size_t clear_from = fused ? p.off_state : p.off_hist;
+  ca.clear = block ? nullptr : (uint4*)(ws + clear_from);
+  ca.n_clear = (int64_t)(p.off_state - clear_from + sizeof(int32_t) * p.rows * 8) / 16;
   HS2_TRY_LAUNCH(KK_COMBINE, s, launch_combine(ca, std::min(16 * p.RT, p.C * p.Gp), p.units, s));
 
   PoolArgs pa{};
@@ -631,6 +635,11 @@ hs2_status full_attn_impl(const hs2_dims* dims, const uint16_t* q, const void* K
   pa.logits = fa.logits;
   pa.logit_stride = p.logit_stride;
   pa.k_stream = p.fa_cache_policy != FA_CACHE_DEFAULT;
+  if (fused) {
+    pa.scores = scores;
+    HS2_TRY_LAUNCH(KK_SCORE_SELECT, s, launch_score_select(sa, pa, s));
+    return HS2_OK;
+  }
   if (p.pool_logits)
     HS2_TRY_LAUNCH(KK_POOL_LOGITS, s, launch_pool_logits(pa, s));
   else

@@ -140,16 +140,17 @@ __device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPla
   // falls as S grows, so the smallest S that fits is the same.
   const int cap_u = (ll.max_len + sp.align - 1) / sp.align;
   const int min_u = (sp.min_split + sp.align - 1) / sp.align;
-  const float n = (float)sp.n_items;
+  const int n_items = sp.n_items;
+  const float n = (float)n_items;
   int lo = max(min_u, (int)(tot * (0.9999f / (n * al))));
   int hi = cap_u;
-  if (sp.n_items > units) hi = min(cap_u, (int)fminf(tot * (1.0001f / ((n - (float)units) * al)), 1e9f) + 1);
+  if (n_items > units) hi = min(cap_u, (int)fminf(tot * (1.0001f / ((n - (float)units) * al)), 1e9f) + 1);
   hi = max(hi, lo);  // items(lo) <= items(hi) when hi is raised to lo
   lo = __builtin_amdgcn_readfirstlane(lo);
   hi = __builtin_amdgcn_readfirstlane(hi);
   while (lo < hi) {
     const int mid = (lo + hi) / 2;
-    if (fa_items_of(ll, Hkv, mid * sp.align) <= sp.n_items)
+    if (fa_items_of(ll, Hkv, mid * sp.align) <= n_items)
       hi = mid;
     else
       lo = mid + 1;
@@ -1204,6 +1205,7 @@ constexpr size_t SEL_BM_LDS_MAX = 65536; // largest row bitmap kept in LDS (5242
 constexpr int SEL_FUSED_TOKENS = SEL_PER * SELB;
 static_assert(NBINS == SELB, "one histogram bin per thread");
 
+constexpr int RANK_MAX = 64;             // candidates ranked directly instead by one wave (256: 1.5 us slower than radix passes)
 constexpr int RDX_BITS = 11;             // digit width of the candidates' radix select
 constexpr int RDX_BINS = 1 << RDX_BITS;  // two histogram bins per thread
 static_assert(RDX_BINS == 2 * SELB, "two radix bins per thread");
@@ -1313,6 +1315,25 @@ __device__ inline void resolve_row(const SelArgs& a, int64_t row, int need, int 
   };
   if (in_lds && !comp_ready)  // (comp_ready: the caller built them in LDS)
     for (int i = tid; i < m; i += SELB) sh.u.comp[i] = ((uint64_t)ck[i] << 32) | (uint32_t)(~ci[i]);
+  if (m <= RANK_MAX) {
+    // few candidates: each one's rank among them says whether it is taken
+    // (composites are distinct); no passes, no scans
+    __syncthreads();
+    if (tid < m) {
+      const uint64_t cv = sh.u.comp[tid];
+      int larger = 0;
+#pragma unroll 8
+      for (int j = 0; j < m; ++j) larger += sh.u.comp[j] > cv;
+      if (larger < need) {
+        const int t = (int)~(uint32_t)cv;
+        if (sbm)
+          atomicOr((unsigned long long*)&sbm[t >> 6], 1ull << (t & 63));
+        else
+          atomicOr(&bm32[t >> 5], 1u << (t & 31));
+      }
+    }
+    return;
+  }
   uint64_t thresh = 0;  // composite of the need-th largest (0: take every candidate)
   if (need < m) {
     uint64_t prefix = rs.prefix, pmask = rs.pmask;
@@ -1673,32 +1694,12 @@ __global__ __launch_bounds__(SELB) void k_sel_finish(SelArgs a) {
   emit_row(a, row, ri, sh, BM_LDS ? sbm : nullptr);
 }
 
-// Rows of at most SEL_FUSED_TOKENS candidates: one workgroup per row filters
-// every chunk into an LDS bitmap and LDS candidate list, then selects and
-// emits (one launch; the two-kernel path above serves longer rows, whose
-// chunks need more workgroups).
-__global__ __launch_bounds__(SELB) void k_sel_fused(SelArgs a) {
-  __shared__ SelShared sh;
-  extern __shared__ __align__(16) uint64_t sbm[];
-  const int64_t row = blockIdx.x;
-  const RowInfo ri = row_info(a, row);
-  const float* P = a.scores + row * a.score_stride;
-  int* st = a.state + row * 8;
+// The end of a one-workgroup row: its LDS candidates (cand list, overflow in
+// global slots) resolved against the threshold, then the emission.
+__device__ inline void finish_lds_row(const SelArgs& a, int64_t row, const RowInfo& ri, const Threshold& th,
+                                      SelShared& sh, uint64_t* sbm) {
   const int tid = threadIdx.x;
-  if (tid == 0) sh.u.cand.n = 0;
-  const Threshold th = find_threshold(a, row, ri, sh);
-  const DigitBounds db = digit_bounds(th);
-  __syncthreads();  // the list initialised (find_threshold may return before its barriers)
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (int t0 = 0; t0 < ri.N; t0 += SEL_TOKENS) {
-    const int t1 = min(ri.N, t0 + SEL_TOKENS);
-    const int wt0 = t0 + 64 * SEL_PER * wave;
-    if (wt0 < t1) {  // uniform across the wave
-      int v[SEL_PER];
-      load_wave(P, wt0, t1, v);
-      filter_wave<false, SEL_LDS_CAND>(a, row, db, wt0, t1, v, &sh.u.cand, st, sbm);
-    }
-  }
+  int* st = a.state + row * 8;
   __syncthreads();
   const int n = sh.u.cand.n;
   if (th.mode == 2 && n > 0) {
@@ -1730,6 +1731,125 @@ __global__ __launch_bounds__(SELB) void k_sel_fused(SelArgs a) {
   }
   __syncthreads();
   emit_row(a, row, ri, sh, sbm);
+}
+
+// Rows of at most SEL_FUSED_TOKENS candidates: one workgroup per row filters
+// every chunk into an LDS bitmap and LDS candidate list, then selects and
+// emits (one launch; the two-kernel path above serves longer rows, whose
+// chunks need more workgroups).
+__global__ __launch_bounds__(SELB) void k_sel_fused(SelArgs a) {
+  __shared__ SelShared sh;
+  extern __shared__ __align__(16) uint64_t sbm[];
+  const int64_t row = blockIdx.x;
+  const RowInfo ri = row_info(a, row);
+  const float* P = a.scores + row * a.score_stride;
+  int* st = a.state + row * 8;
+  const int tid = threadIdx.x;
+  if (tid == 0) sh.u.cand.n = 0;
+  const Threshold th = find_threshold(a, row, ri, sh);
+  const DigitBounds db = digit_bounds(th);
+  __syncthreads();  // the list initialised (find_threshold may return before its barriers)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (int t0 = 0; t0 < ri.N; t0 += SEL_TOKENS) {
+    const int t1 = min(ri.N, t0 + SEL_TOKENS);
+    const int wt0 = t0 + 64 * SEL_PER * wave;
+    if (wt0 < t1) {  // uniform across the wave
+      int v[SEL_PER];
+      load_wave(P, wt0, t1, v);
+      filter_wave<false, SEL_LDS_CAND>(a, row, db, wt0, t1, v, &sh.u.cand, st, sbm);
+    }
+  }
+  finish_lds_row(a, row, ri, th, sh, sbm);
+}
+
+// Scores and selection of such rows from the stored logits in one launch: the
+// row's workgroup computes its scores (the sums of k_pool_logits, in its
+// order), keeps them in registers, builds the histogram in LDS and selects.
+// The scores go to memory only where the caller asked for them (pa.scores).
+// Latency-bound: a chain of the logits' loads and about ten barriers.  Against
+// k_pool_logits and k_sel_fused (event time): one 4K sequence of 16 / 2 heads
+// 19.6 -> 13.9 us, 64 sequences of 1K-12K tokens, 32 / 8 heads, 42.4 -> 35.1
+// (a loop over tokens with the heads inside kept few loads in flight: 56.9).
+__global__ __launch_bounds__(SELB) void k_score_select(SelArgs a, PoolArgs pa) {
+  __shared__ SelShared sh;
+  __shared__ float s_fac[16], s_msub[16];
+  extern __shared__ __align__(16) uint64_t sbm[];
+  const int64_t row = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = (int)row % a.C;
+  const int64_t unit = row / a.C;
+  const int G = pa.G;
+  uint32_t* hist = sh.h;  // NBINS of its RDX_BINS words, until the threshold is known
+  hist[tid] = 0;
+  if (tid == 0) sh.u.cand.n = 0;
+  if (tid < G) {
+    const int b = (int)(unit / a.Hkv), g = (int)(unit % a.Hkv);
+    const float2 mz = *(const float2*)(pa.stats_log2 + (((int64_t)b * a.C + c) * pa.Hq + (int64_t)g * G + tid) * 2);
+    const bool big = !(fabsf(mz.x) < 64.f);
+    s_fac[tid] = mz.y > 0.f ? (big ? 1.f / mz.y : fast_exp2(-mz.x) / mz.y) : 0.f;
+    s_msub[tid] = (mz.y > 0.f && big) ? mz.x : 0.f;
+  }
+  const RowInfo ri = row_info(a, row);
+  // words of 64 tokens, the same count for each of the 16 waves
+  const int per = (((ri.N + 63) >> 6) + SELB / 64 - 1) / (SELB / 64);
+  const int wt0 = 64 * per * wave;
+  const int t1 = min(ri.N, wt0 + 64 * per);
+  const float* lg = pa.logits + (unit * a.C + c) * G * pa.logit_stride;
+  __syncthreads();
+  int v[SEL_PER];
+#pragma unroll
+  for (int j = 0; j < SEL_PER; ++j) v[j] = 0;
+  // NW >= per words at once, head by head: a head's NW loads are in flight
+  // together with the next head's
+  auto score = [&](auto nw) __attribute__((always_inline)) {
+    constexpr int NW = decltype(nw)::value;
+    const int last = max(t1 - 1, 0);
+    int at[NW];
+    float acc[NW], cur[NW], nxt[NW];
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      at[j] = min(wt0 + 64 * j + lane, last);  // past the end: a token of the row, not used
+      acc[j] = 0.f;
+      cur[j] = lg[at[j]];
+    }
+    for (int h = 0; h < G; ++h) {
+      const float* next = lg + (h + 1 < G ? h + 1 : h) * pa.logit_stride;
+#pragma unroll
+      for (int j = 0; j < NW; ++j) nxt[j] = next[at[j]];
+      const float m = s_msub[h], f = s_fac[h];
+#pragma unroll
+      for (int j = 0; j < NW; ++j) {
+        acc[j] += fast_exp2(cur[j] - m) * f;
+        cur[j] = nxt[j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NW; ++j) {
+      const int t = wt0 + 64 * j + lane;
+      if (t < t1) {
+        v[j] = __float_as_int(acc[j]);
+        if (pa.scores) pa.scores[row * pa.score_stride + t] = acc[j];
+        atomicAdd(&hist[score_digit(acc[j])], 1u);
+      }
+    }
+  };
+  if (wt0 < t1) {  // uniform across the wave
+    if (per <= 4)
+      score(std::integral_constant<int, 4>{});
+    else if (per <= 8)
+      score(std::integral_constant<int, 8>{});
+    else
+      score(std::integral_constant<int, SEL_PER>{});
+  }
+  __syncthreads();
+  const int cnt = (int)hist[NBINS - 1 - tid];
+  const Threshold th = find_threshold(cnt, ri, sh);
+  const DigitBounds db = digit_bounds(th);
+  __syncthreads();  // (find_threshold may return before its barriers)
+  if (wt0 < t1)  // uniform across the wave
+    filter_wave<false, SEL_LDS_CAND>(a, row, db, wt0, t1, v, &sh.u.cand, a.state + row * 8, sbm);
+  finish_lds_row(a, row, ri, th, sh, sbm);
 }
 
 // ---------------------------------------------------------------------------- block-level selection
@@ -2646,6 +2766,14 @@ hipError_t launch_block_select(const BlockSelArgs& a, hipStream_t s) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   HS2_LAUNCH(k_block_select, dim3((unsigned)a.rows), dim3(SELB), nb_max * sizeof(uint32_t), s, a);
+  return hipGetLastError();
+}
+
+bool score_select_serves(int max_len) { return max_len <= SEL_FUSED_TOKENS; }
+hipError_t launch_score_select(const SelArgs& a, const PoolArgs& pa, hipStream_t s) {
+  if (!score_select_serves(a.max_len) || pa.G > 16) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_score_select, dim3((unsigned)a.rows), dim3(SELB), (size_t)a.bitmap_words * sizeof(uint64_t), s, a,
+                     pa);
   return hipGetLastError();
 }
 

@@ -156,6 +156,10 @@ hipError_t set_pool_smem_limits();
 hipError_t launch_sel_init(const SelArgs& a, hipStream_t s);
 hipError_t launch_sel_hist(const SelArgs& a, int nchunks, hipStream_t s);
 hipError_t launch_select(const SelArgs& a, hipStream_t s);
+// scores from the stored logits and selection in one launch, for rows of at
+// most 16384 tokens (score_select_serves); pa.scores: where the scores go, or null
+bool score_select_serves(int max_len);
+hipError_t launch_score_select(const SelArgs& a, const PoolArgs& pa, hipStream_t s);
 hipError_t launch_block_select(const BlockSelArgs& a, hipStream_t s);  // block sums + selection
 hipError_t launch_sa_split(const SaArgs& a, int RT, hipStream_t s);
 // sparse layer with one workgroup of NW (4 or 8) waves per (sequence, KV head,

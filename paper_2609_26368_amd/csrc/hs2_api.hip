@@ -214,6 +214,7 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   const int align = fa_split_align(p.RT, p.fa_variant);
   p.fa_sp.align = align;
   p.fa_sp.min_split = (int)round_up(256, align);
+  p.fa_sp.few_items = (int)std::min<int64_t>(di ? di->cus : 256, slots);
   const int fixed = env_int("HS2_FA_SPLIT", 0);
   if (fixed > 0) {
     p.fa_sp.fixed = (int)std::max<int64_t>(align, round_up(std::min<int64_t>(fixed, p.Lmax), align));

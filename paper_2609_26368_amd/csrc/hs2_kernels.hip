@@ -607,17 +607,21 @@ __device__ inline void store_out4(float4 o, float Z, float v_scale, const uint2*
 // HDIM / 4 column quads.
 // FA: unit = (b, g), row r = c * Gp + h; slots valid = ceil(Lv / split) * TG.
 // SA: unit = (b, g, c), row = h; all n_split * TG slots written.
-template <int HDIM>
+// ROWS (FA, few partials a row, many rows): grid (ceil(rows_per_unit / SG),
+// units), each slot group merges a row of its own, with no exchange: a
+// workgroup per row is mostly its start (one partial a row: 512 KV heads of 64
+// query rows 58 -> 14 us, 1024 heads 133 -> 26; 512 heads of 4 rows 11.4 -> 8.4).
+template <int HDIM, bool ROWS>
 __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
   constexpr int NQ = HDIM / 4, SG = 256 / NQ;
   __shared__ float s_m[SG], s_mt[SG], s_z[SG];
   __shared__ float4 s_o[SG][NQ];
-  const int r = blockIdx.x;
   const int64_t unit = blockIdx.y;
   const int tid = threadIdx.x;
   const int sg = tid / NQ, dq = tid % NQ;
+  const int r = ROWS ? blockIdx.x * SG + sg : blockIdx.x;
   if (a.clear) {  // zero the selection histogram and counters for the kernels that follow
-    const int64_t nb = (int64_t)gridDim.x * gridDim.y, bid = unit * gridDim.x + r;
+    const int64_t nb = (int64_t)gridDim.x * gridDim.y, bid = unit * gridDim.x + blockIdx.x;
     for (int64_t i = bid * 256 + tid; i < a.n_clear; i += nb * 256) a.clear[i] = make_uint4(0, 0, 0, 0);
   }
   int b, g, c, h;
@@ -632,7 +636,8 @@ __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
     c = r / a.Gp;
     h = r % a.Gp;
   }
-  if (c >= a.C || h >= a.G) return;
+  const bool valid = c < a.C && h < a.G;
+  if (!ROWS && !valid) return;
   int nvalid = a.nslot;
   int64_t base = unit * a.nslot * a.rows + r;
   if (!a.sa_mode) {  // the full-attention items of (b, g): their slots are contiguous
@@ -642,13 +647,14 @@ __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
     nvalid = ((Lv + S - 1) / S) * a.tg;
     base = (int64_t)fa_first_item(ll, a.Hkv, S, b, g) * a.tg * a.rows + r;
   }
+  if (ROWS && !valid) return;  // (after the wave's shared split search)
   // one pass over the partials: each slot group merges its slots online
   // (reference maximum m, sum l, output row, rescaled when m rises) with
   // every slot's loads issued together, then the groups are merged in LDS
   float m = -INFINITY, mt = -INFINITY, z = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 4
-  for (int s = sg; s < nvalid; s += SG) {
+  for (int s = ROWS ? 0 : sg; s < nvalid; s += ROWS ? 1 : SG) {
     const int64_t pr = base + (int64_t)s * a.rows;
     const float4 ml = *(const float4*)(a.part_ml + pr * 4);
     const float4 o = *(const float4*)(a.part_o + pr * HDIM + 4 * dq);
@@ -664,37 +670,47 @@ __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
     acc.w = acc.w * keep + o.w * w;
     m = mn;
   }
-  if (dq == 0) {
-    s_m[sg] = m;
-    s_mt[sg] = mt;
-  }
-  __syncthreads();
-  float M = -INFINITY, Mt = -INFINITY;
-#pragma unroll
-  for (int j = 0; j < SG; ++j) {
-    M = fmaxf(M, s_m[j]);
-    Mt = fmaxf(Mt, s_mt[j]);
-  }
   const int64_t orow = ((int64_t)b * a.C + c) * a.Hq + (int64_t)g * a.G + h;
   // sink logit of this head in log2 units: joins the normaliser, no value row
   const float sink2 = a.sink ? a.sink[g * a.G + h] * 1.4426950408889634f : -INFINITY;
-  M = fmaxf(M, sink2);
-  const float f = M == -INFINITY ? 0.f : fast_exp2(m - M);  // this group's share
-  s_o[sg][dq] = make_float4(acc.x * f, acc.y * f, acc.z * f, acc.w * f);
-  if (dq == 0) s_z[sg] = z * f;
-  __syncthreads();
-  if (sg != 0) return;
-  float Z = 0.f;
-  float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  float M, Mt, Z;
+  float4 o;
+  if constexpr (ROWS) {  // (no sparse layer: no sink)
+    M = m;
+    Mt = mt;
+    Z = z;
+    o = acc;
+  } else {
+    if (dq == 0) {
+      s_m[sg] = m;
+      s_mt[sg] = mt;
+    }
+    __syncthreads();
+    M = -INFINITY;
+    Mt = -INFINITY;
 #pragma unroll
-  for (int j = 0; j < SG; ++j) {
-    Z += s_z[j];
-    o.x += s_o[j][dq].x;
-    o.y += s_o[j][dq].y;
-    o.z += s_o[j][dq].z;
-    o.w += s_o[j][dq].w;
+    for (int j = 0; j < SG; ++j) {
+      M = fmaxf(M, s_m[j]);
+      Mt = fmaxf(Mt, s_mt[j]);
+    }
+    M = fmaxf(M, sink2);
+    const float f = M == -INFINITY ? 0.f : fast_exp2(m - M);  // this group's share
+    s_o[sg][dq] = make_float4(acc.x * f, acc.y * f, acc.z * f, acc.w * f);
+    if (dq == 0) s_z[sg] = z * f;
+    __syncthreads();
+    if (sg != 0) return;
+    Z = 0.f;
+    o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < SG; ++j) {
+      Z += s_z[j];
+      o.x += s_o[j][dq].x;
+      o.y += s_o[j][dq].y;
+      o.z += s_o[j][dq].z;
+      o.w += s_o[j][dq].w;
+    }
+    if (sink2 != -INFINITY) Z += fast_exp2(sink2 - M);
   }
-  if (sink2 != -INFINITY) Z += fast_exp2(sink2 - M);
   store_out4<HDIM>(o, Z, a.v_scale ? a.v_scale[g] : 1.f, a.gate ? (const uint2*)(a.gate + orow * HDIM) + dq : nullptr,
                    a.out, orow, dq);
   if (dq == 0) {
@@ -2746,11 +2762,24 @@ hipError_t set_pool_smem_limits() {
 }
 
 hipError_t launch_combine(const CombineArgs& a, int rows_per_unit, int64_t units, hipStream_t s) {
-  if (a.hd == 256)
-    HS2_LAUNCH(k_combine<256>, dim3(rows_per_unit, (unsigned)units), dim3(256), 0, s, a);
-  else
-    HS2_LAUNCH(k_combine<128>, dim3(rows_per_unit, (unsigned)units), dim3(256), 0, s, a);
-  return hipGetLastError();
+  // a slot group per row where a row has at most about 8 partials (one per
+  // group otherwise) and there are rows enough to fill the chip that way
+  const int sg = 256 / (a.hd / 4);
+  const bool rows = !a.sa_mode && a.sp.fixed == 0 && (int64_t)a.sp.n_items * a.tg <= 8 * units &&
+                    (int64_t)rows_per_unit * units >= 2048;
+  const dim3 grid((unsigned)(rows ? (rows_per_unit + sg - 1) / sg : rows_per_unit), (unsigned)units);
+#define HS2_COMBINE(hdim)                                                      \
+  if (a.hd == hdim) {                                                          \
+    if (rows)                                                                  \
+      HS2_LAUNCH((k_combine<hdim, true>), grid, dim3(256), 0, s, a);           \
+    else                                                                       \
+      HS2_LAUNCH((k_combine<hdim, false>), grid, dim3(256), 0, s, a);          \
+    return hipGetLastError();                                                  \
+  }
+  HS2_COMBINE(128)
+  HS2_COMBINE(256)
+#undef HS2_COMBINE
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_sel_init(const SelArgs& a, hipStream_t s) {

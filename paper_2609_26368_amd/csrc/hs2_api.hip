@@ -210,11 +210,29 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   // the capacity).
   const int lrt = p.RT >= 8 ? 3 : p.RT >= 4 ? 2 : p.RT >= 2 ? 1 : 0;
   const int wgs_cu = di && di->fa_wgs[kv8][lrt][p.fa_variant] > 0 ? di->fa_wgs[kv8][lrt][p.fa_variant] : 4;
-  const int64_t slots = (int64_t)(di ? di->cus : 256) * wgs_cu * std::max(1, env_int("HS2_FA_ROUNDS", 1));
+  const int64_t round = (int64_t)(di ? di->cus : 256) * wgs_cu;
+  // With few splits a KV head in one round, ragged lengths cannot be balanced
+  // (and 512 equal ones leave a third of 768 slots idle): up to four rounds
+  // where the partials are small.  One row tile: about four splits a KV head
+  // (64 sequences of 1K-12K tokens, 8 KV heads: 376 us in one round, 351,
+  // 346, 345 in two, three, four; 1024 KV heads of up to 3K: 219 -> 181); at
+  // head dim 256, whose equal lengths lose up to 3 % below that, only from a
+  // KV head per slot on (1024 heads of 3K: 659 -> 584, ragged 407 -> 336).
+  // Two row tiles: about two splits a KV head from 0.6 heads per slot on (512
+  // heads of 5K 255 -> 226, 1024 ragged ones 279 -> 190; 384 heads would
+  // lose, 185 -> 201).  More row tiles lose throughout (64 rows, 512 heads of
+  // 5K: 212 -> 219 -> 236).
+  int64_t balance = 1;
+  if (p.RT == 1 && (p.D == 128 || p.units > round))
+    balance = cdiv(4 * p.units, round);
+  else if (p.RT == 2 && p.D == 128 && 5 * p.units >= 3 * round)
+    balance = cdiv(2 * p.units, round);
+  balance = std::min<int64_t>(4, std::max<int64_t>(1, balance));
+  const int64_t slots = round * std::max(1, env_int("HS2_FA_ROUNDS", (int)balance));
   const int align = fa_split_align(p.RT, p.fa_variant);
   p.fa_sp.align = align;
   p.fa_sp.min_split = (int)round_up(256, align);
-  p.fa_sp.few_items = (int)std::min<int64_t>(di ? di->cus : 256, slots);
+  p.fa_sp.few_items = (int)std::min<int64_t>(di ? di->cus : 256, round);
   const int fixed = env_int("HS2_FA_SPLIT", 0);
   if (fixed > 0) {
     p.fa_sp.fixed = (int)std::max<int64_t>(align, round_up(std::min<int64_t>(fixed, p.Lmax), align));

@@ -1,0 +1,23 @@
+"""Many KV heads at once: the merge with a row per slot group (at least 2048
+rows of at most about 8 partials), and the full-attention splits sized for
+several rounds of workgroups (more than a quarter, or 0.6, of a round's slots
+in KV heads), ragged down to the chunk itself, in both cache formats."""
+from __future__ import annotations
+
+import pytest
+
+from paper_2609_26368_amd import workloads as W
+from tests.test_gpu_parity import parity_case
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [  # B, Hkv, G, C, D, ctx, kv
+    (48, 4, 16, 1, 128, 400, "bf16"), (64, 8, 4, 1, 128, 700, "bf16"), (64, 8, 5, 1, 128, 700, "fp8"),
+    (64, 8, 16, 2, 128, 300, "bf16"), (40, 4, 3, 6, 256, 300, "bf16"), (65, 3, 8, 8, 128, 200, "fp8"),
+    (100, 8, 4, 1, 256, 600, "bf16"),
+]
+
+
+@pytest.mark.parametrize("B,Hkv,G,C,D,ctx,kv", SHAPES, ids=["b%d_kv%d_g%d_c%d_d%d_%s" % (s[:5] + s[6:]) for s in SHAPES])
+def test_many_kv_heads(B, Hkv, G, C, D, ctx, kv):
+    parity_case(W.Workload("many_heads", B, ctx, C, G * Hkv, Hkv, D, 40, 20, 1, ctx_min=C), seed=51, kv=kv)

@@ -66,8 +66,8 @@ int env_int(const char* name, int dflt) {
 struct Plan {
   int B, C, Hq, Hkv, G, Gp, D, Lmax, k, W, S;
   float c2;
-  int RT, TG;                 // full-attention / pooling row tiles
-  int fa_variant;             // ring kernel shape (0, 2, 3, 4) for RT <= 4; 1: workgroup kernel
+  int RT;                     // full-attention / pooling row tiles
+  int fa_variant;             // full-attention kernel shape (HS2_RING_VARIANTS)
   FaSplitPlan fa_sp;          // full-attention token splits (grid: fa_sp.n_items items)
   int fa_cache_policy;  // FaCachePolicy of the full-attention ring kernel
   int fa_k_keep;        // FA_STREAM_K_HEAD: percent of each token group's K rows kept cacheable
@@ -86,7 +86,7 @@ struct Plan {
 };
 
 struct SaPlan {
-  int RT, TG, split, nsplit, n_slots;
+  int RT, split, nsplit, n_slots;
   int unit_waves;  // waves of the sa_unit kernel, 0: the split kernel
   size_t off_part_o, off_part_ml, bytes;
 };
@@ -162,18 +162,17 @@ int ilog2(int v) {
 // Measured on MI355X with one-round splits: 32-token tiles in 3 stages for
 // one row tile; 16-token tiles in 3 stages and two token groups merged in
 // LDS (half the split partials) for two; for four, one row tile per wave
-// (four waves), 32-token tiles in 2 stages and two token groups; the
-// workgroup kernel for eight.  Head dim 256: one row tile per wave, four
+// (four waves), 32-token tiles in 2 stages and two token groups; for eight,
+// one row tile per wave (eight waves) and 64-token tiles in 2 stages (16
+// queries of 8 heads, 4 x 64K tokens, 4 KV heads: 103 us against 173 for a
+// kernel with four stages and one workgroup per compute unit).  Head dim 256: one row tile per wave, four
 // row tiles in 32-token tiles and 2 stages, fewer in 16-token tiles and 3
 // stages.  The one-row-tile shape serves both cache formats (E4M3 at 512K:
 // 0.624 ms per step against 0.639 with 16-token tiles in 3 stages, whose
 // stored logits also make the score pass slower, 69 against 59 us).
-int default_fa_variant(int RT, int hd, bool kv8) {
+int default_fa_variant(int RT, int hd) {
   if (hd == 256) return RT >= 4 ? 8 : 6;
-  if (RT >= 8) return kv8 ? 7 : 1;
-  if (RT == 1) return 2;
-  if (RT == 4) return 7;
-  return 5;
+  return RT >= 4 ? 7 : RT == 1 ? 2 : 5;
 }
 
 // kv8: the cache is E4M3 (ring kernels only)
@@ -194,10 +193,9 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   p.c2 = (float)(scale * 1.4426950408889634);
   const int rows16 = (int)cdiv(p.C * p.Gp, 16);
   p.RT = next_pow2(rows16);
-  p.fa_variant = env_int("HS2_FA_VARIANT", default_fa_variant(p.RT, p.D, kv8));
+  p.fa_variant = env_int("HS2_FA_VARIANT", default_fa_variant(p.RT, p.D));
   if (p.fa_variant < 0 || p.fa_variant >= kFaVariants || fa_variant_head_dim(p.RT, p.fa_variant, kv8) != p.D)
-    p.fa_variant = default_fa_variant(p.RT, p.D, kv8);
-  p.TG = fa_token_groups(p.RT, p.fa_variant);
+    p.fa_variant = default_fa_variant(p.RT, p.D);
   p.units = (int64_t)p.B * p.Hkv;
   p.rows = p.units * p.C;
   // token splits: one item (sequence, KV head, split) per workgroup of a
@@ -257,7 +255,7 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   // with at most 16 query rows per KV head (C * G <= 16) the ring kernel
   // stores its logits (4 C G bytes per token) and the scores are computed
   // from them instead of re-reading K (256 bytes per token)
-  p.pool_logits = p.RT == 1 && p.fa_variant != 1 && env_int("HS2_POOL_FROM_K", 0) == 0;
+  p.pool_logits = p.RT == 1 && env_int("HS2_POOL_FROM_K", 0) == 0;
   p.logit_stride = round_up(p.Lmax, 64);
   // Cache policy of the full-attention ring kernel's loads.  A cache that
   // fits the last-level cache keeps every row cacheable (a decode loop finds
@@ -288,7 +286,7 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
       4096, std::max<int64_t>(1024, round_up(cdiv(p.Lmax * p.units, 2 * (int64_t)(di ? di->cus : 256)), 1024)));
 
   const int64_t prow = 16 * p.RT;
-  const int64_t nslot = (int64_t)p.fa_sp.n_items * p.TG;  // partial slots of the full-attention pass
+  const int64_t nslot = p.fa_sp.n_items;  // partial slots of the full-attention pass
   size_t cur = 0;
   p.off_part_o = carve(cur, sizeof(float) * nslot * prow * p.D);
   p.off_part_ml = carve(cur, sizeof(float) * nslot * prow * 4);
@@ -306,7 +304,6 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
 void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   s.n_slots = n_slots;
   s.RT = next_pow2((int)cdiv(p.Gp, 16));
-  s.TG = 1;  // one partial per split
   // about 1024 workgroups, at most 4096 slots each (their indices are staged in LDS)
   int split = (int)std::max<int64_t>(64, round_up(cdiv(p.rows * (int64_t)n_slots, 1024), 64));
   split = env_int("HS2_SA_SPLIT", split);
@@ -336,7 +333,7 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
     s.nsplit = (int)cdiv(n_slots, kSaUnitSlots);
     s.split = (int)round_up(cdiv(n_slots, s.nsplit), 16);
   }
-  const int64_t parts = p.rows * std::max(s.nsplit, split_nsplit) * s.TG * prow;
+  const int64_t parts = p.rows * std::max(s.nsplit, split_nsplit) * prow;
   s.off_part_o = carve(cur, sizeof(float) * parts * p.D);
   s.off_part_ml = carve(cur, sizeof(float) * parts * 4);
   s.bytes = (size_t)round_up((int64_t)cur, kAlign);
@@ -613,7 +610,6 @@ hs2_status full_attn_impl(const hs2_dims* dims, const uint16_t* q, const void* K
   ca.max_len = p.Lmax;
   ca.rows = 16 * p.RT;
   ca.nslot = 0;  // per (sequence, KV head): derived in the kernel from the splits
-  ca.tg = p.TG;
   ca.sp = p.fa_sp;
   ca.sa_mode = 0;
   ca.v_scale = v_scale;
@@ -833,8 +829,7 @@ hs2_status sparse_impl(const hs2_dims* dims, const uint16_t* q, const void* K, c
   ca.Gp = p.Gp;
   ca.max_len = p.Lmax;
   ca.rows = 16 * sp.RT;
-  ca.nslot = sp.nsplit * sp.TG;
-  ca.tg = sp.TG;
+  ca.nslot = sp.nsplit;
   ca.sa_mode = 1;
   ca.sink = sink;
   ca.gate = gate;

@@ -27,8 +27,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int HD = 128;         // head dim of the workgroup kernel; the ring kernels take theirs as a parameter
-constexpr int TILE = 64;        // cache rows per LDS stage of the workgroup kernel
+constexpr int HD = 128;         // default head dim of the templates below
 constexpr int NT = 256;         // threads per workgroup of the score and histogram kernels
 constexpr int SEL_CHUNK = 4096;  // tokens per workgroup of the selection scans
 constexpr int NBINS = 1024;     // first-level radix bins of the pooled-score keys
@@ -215,8 +214,8 @@ __device__ inline void store_partial(const WaveState<RPW, HDIM>& st, float* __re
 
 
 // ---------------------------------------------------------------- direct-to-LDS staging (swizzled)
-// One stage holds TILE cache rows of K then TILE rows of V, 256 bytes each,
-// row-major; the 16-byte chunk c of row r sits at position c ^ stage_swz(r)
+// One stage holds cache rows of K then as many of V, row-major; the 16-byte
+// chunk c of row r sits at position c ^ stage_swz(r)
 // of the row.  stage_swz(r) mod 8 is a permutation of rows 0-7 and of rows
 // 8-15, so one chunk of 8 consecutive rows (the MFMA K-operand reads) lands
 // in 8 distinct slots of a 128-byte window; its bits 1-2 are r & 3, so the
@@ -224,29 +223,16 @@ __device__ inline void store_partial(const WaveState<RPW, HDIM>& st, float* __re
 // as well; and it is a permutation of all 16 rows.  With it both reads were
 // measured free of bank conflicts (with c ^ (r & 15) the V reads were
 // 2-way).  A wave's 16-byte direct LDS load writes 64 consecutive 16-byte
-// slots (lane order): load n = 4 * wave + u fills slots 64 n + lane, i.e.
-// row 4 n + lane / 16, position lane % 16.
+// slots (lane order).
 __device__ __host__ constexpr int stage_swz(int r) {
   return ((r & 3) << 1) | (((r >> 2) & 1) << 3) | (((r >> 2) ^ (r >> 3)) & 1);
 }
-constexpr int STAGE_ROW_BYTES = HD * 2;
-constexpr int STAGE_KV_BYTES = TILE * STAGE_ROW_BYTES;  // 16 KB
-constexpr int STAGE_BYTES = 2 * STAGE_KV_BYTES;         // K + V
-constexpr int FA_STAGES = 4;
-
 typedef short i16x4_lds __attribute__((ext_vector_type(4)));
-
-// NW waves share the loads of a stage: LPW = 16 / NW loads of 1 KB per
-// matrix per wave; load n = LPW * wave + u fills rows 4 n .. 4 n + 3.
-template <int NW>
-__device__ inline int stage_row(int wave, int u, int lane) {
-  return 4 * ((16 / NW) * wave + u) + (lane >> 4);
-}
 
 // One 16-byte-per-lane direct LDS load: lane i's 16 bytes from `src` land at
 // LDS byte address lds_base + 16 i.  Issued as inline assembly so that the
 // compiler does not guard every later LDS read with a wait for all
-// outstanding loads; the caller waits explicitly (wait_stage_loads) and
+// outstanding loads; the caller waits explicitly (wait_ring) and
 // then synchronises the workgroup before reading the stage.
 __device__ inline void dma16(const void* src, uint32_t lds_base) {
   asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds_base) : "memory");
@@ -283,39 +269,6 @@ __device__ inline uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
-// Issue this wave's share of one stage: rows tok[u] (u < 16 / NW) of K and V.
-template <int NW>
-__device__ inline void issue_stage_loads(unsigned char* stage, const uint16_t* Kbg, const uint16_t* Vbg,
-                                         int64_t stride_t, const int* tok, int wave, int lane) {
-  constexpr int LPW = 16 / NW;
-  const uint32_t base = lds_addr(stage);
-#pragma unroll
-  for (int u = 0; u < LPW; ++u) {
-    const int n = LPW * wave + u;
-    const int r = stage_row<NW>(wave, u, lane);
-    const int c = (lane & 15) ^ stage_swz(r);
-    const int64_t off = (int64_t)tok[u] * stride_t + 8 * c;
-    dma16(Kbg + off, __builtin_amdgcn_readfirstlane(base + 1024 * n));
-    dma16(Vbg + off, __builtin_amdgcn_readfirstlane(base + STAGE_KV_BYTES + 1024 * n));
-  }
-}
-
-// s_waitcnt until at most `tiles` stages of this wave's loads (2 * 16 / NW
-// each) are outstanding.  gfx9 encoding: vmcnt = bits [3:0] | [15:14];
-// expcnt [6:4] and lgkmcnt [11:8] stay at their maxima.
-template <int NW>
-__device__ inline void wait_stage_loads(int tiles) {
-  if (NW == 4) {
-    if (tiles <= 0) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
-    else if (tiles == 1) __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8)
-    else __builtin_amdgcn_s_waitcnt(0x4F70);                  // vmcnt(16)
-  } else {
-    if (tiles <= 0) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0)
-    else if (tiles == 1) __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4)
-    else __builtin_amdgcn_s_waitcnt(0x0F78);                  // vmcnt(8)
-  }
-}
-
 // The k order of the logits MFMAs (16x16x32): for MFMA kk, lane group
 // j = lane / 16 holds the 8 head dims 64 (kk / 2) + 16 j + 8 (kk % 2) .. + 7,
 // in the K operands and the query operands alike.  So MFMAs 2 i and 2 i + 1
@@ -342,35 +295,6 @@ __device__ inline void qk_block_swz(const unsigned char* stg, int blk, const uin
     S[rr] = acc;
   }
 }
-
-// V operand of P.V for block blk, columns 16 nb .. 16 nb + 15 (16x16x16 B layout),
-// read transposed from the row-major stage.
-__device__ inline uint2 v_operand_tr(const unsigned char* stg, int blk, int nb, int lane) {
-  const int kq = lane & 15;
-  const int row = 16 * blk + 4 * (lane >> 4) + (kq >> 2);
-  const int col = 16 * nb + 4 * (kq & 3);
-  const int pos = (col >> 3) ^ stage_swz(row);
-  const unsigned char* p = stg + STAGE_KV_BYTES + row * STAGE_ROW_BYTES + 16 * pos + 2 * (col & 7);
-  const i16x4_lds v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4_lds*)(p));
-  return __builtin_bit_cast(uint2, v);
-}
-
-template <int RPW, int BPW>
-__device__ inline void softmax_pv_swz(WaveState<RPW>& st, const unsigned char* stg, const int (&blk)[BPW],
-                                      f32x4 (&S)[BPW][RPW], int lane) {
-  PFrags<BPW, RPW, false> pf;
-  online_softmax(st, S, pf, lane);
-#pragma unroll
-  for (int bi = 0; bi < BPW; ++bi) {
-#pragma unroll
-    for (int nb = 0; nb < 8; ++nb) {
-      const uint2 vb = v_operand_tr(stg, blk[bi], nb, lane);
-#pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) st.o[rr][nb] = mfma_k16(pf.h[bi][rr], vb, st.o[rr][nb]);
-    }
-  }
-}
-
 
 // ---------------------------------------------------------------- wave-private staging
 // A one-wave workgroup streams its own token range through a private ring of

@@ -4,8 +4,6 @@
 //                 LDS rings (bf16 or E4M3 cache, head dim 128 or 256): per
 //                 (sequence, KV head, token split) a partial (m, l, O) of every
 //                 query row of the group; optionally each row's logits
-//   k_fa_split    the same with 64-row stages shared by 4 or 8 waves (up to
-//                 128 query rows per KV head, bf16, head dim 128)
 //   k_combine     merge of the partials -> bf16 output and (M, Z) per query
 //                 row (sparse layers: sink logits, output gates)
 //   k_pool        re-reads K, recomputes the same logits, turns them into exact
@@ -203,107 +201,6 @@ __device__ inline int fa_first_item(const LaneLens& ll, int Hkv, int S, int b, i
 }
 
 // ============================================================================ full attention
-// grid (items), 64 * NW threads, dynamic LDS = FA_STAGES * STAGE_BYTES.
-// Cache rows stream global -> LDS with no register staging (16-byte direct
-// LDS loads), FA_STAGES - 1 tiles in flight while one is computed; a single
-// barrier per tile.  NW = 4 waves for up to 32 query rows, 8 above (two
-// waves per SIMD).  The waves form RTW row-tile groups x TGN token groups:
-// each wave owns RPW row tiles and BPW of the four 16-row blocks of a tile.
-template <int RT>
-struct FaShape {
-  static constexpr int NW = RT >= 4 ? 8 : 4;
-  static constexpr int RTW = RT < NW ? RT : NW;
-  static constexpr int TGN = NW / RTW;
-  static constexpr int RPW = RT / RTW;
-  static constexpr int BPW = 4 / TGN;
-};
-
-template <int RT>
-__global__ __launch_bounds__(512) void k_fa_split(FaArgs a) {
-  using SH = FaShape<RT>;
-  constexpr int NW = SH::NW, RPW = SH::RPW, BPW = SH::BPW, TG = SH::TGN, RTW = SH::RTW;
-  constexpr int LPW = 16 / NW;
-  extern __shared__ __align__(16) unsigned char smem[];
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const LaneLens ll(a.len, a.B, a.max_len);
-  const int S = fa_split_len(ll, a.Hkv, a.sp);
-  int b, g, split;
-  if (!fa_locate(ll, a.Hkv, S, blockIdx.x, b, g, split)) return;
-  const int Lv = clamp_len(a.len, b, a.max_len);
-  const int t_begin = split * S;
-  const int t_end = min(Lv, t_begin + S);
-  const int ntiles = (t_end - t_begin + TILE - 1) / TILE;
-  const int tg = wave / RTW;
-  const int rt0 = (wave % RTW) * RPW;
-
-  uint4 q[RPW][4];
-#pragma unroll
-  for (int rr = 0; rr < RPW; ++rr) load_q_tile(q[rr], a.q, rt0 + rr, lane, a.Gp, a.G, a.C, a.Hq, g, b);
-  // causal position of each of this lane's query rows (padding rows see everything)
-  int rpos[RPW];
-#pragma unroll
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int c = (16 * (rt0 + rr) + (lane & 15)) / a.Gp;
-    rpos[rr] = c < a.C ? Lv - a.C + c : Lv - 1;
-  }
-  const int min_pos = Lv - a.C;
-
-  const int64_t kvoff = (int64_t)b * a.stride_b + (int64_t)g * a.stride_h;
-  const uint16_t* Kbg = a.K + kvoff;
-  const uint16_t* Vbg = a.V + kvoff;
-
-  auto issue = [&](int tile) {
-    const int t0 = t_begin + tile * TILE;
-    int tok[LPW];
-#pragma unroll
-    for (int u = 0; u < LPW; ++u) {
-      const int t = t0 + stage_row<NW>(wave, u, lane);
-      tok[u] = t < t_end ? t : t_end - 1;  // rows past the range repeat a valid row; masked below
-    }
-    issue_stage_loads<NW>(smem + (tile % FA_STAGES) * STAGE_BYTES, Kbg, Vbg, a.stride_t, tok, wave, lane);
-  };
-
-  WaveState<RPW> st;
-  st.init();
-  int blk[BPW];
-#pragma unroll
-  for (int bi = 0; bi < BPW; ++bi) blk[bi] = tg * BPW + bi;
-
-#pragma unroll
-  for (int i = 0; i < FA_STAGES - 1; ++i)
-    if (i < ntiles) issue(i);
-  for (int i = 0; i < ntiles; ++i) {
-    // stages issued after tile i by this wave: min(FA_STAGES - 2, ntiles - 1 - i)
-    wait_stage_loads<NW>(min(FA_STAGES - 2, ntiles - 1 - i));
-    __syncthreads();
-    if (i + FA_STAGES - 1 < ntiles) issue(i + FA_STAGES - 1);
-    const unsigned char* stg = smem + (i % FA_STAGES) * STAGE_BYTES;
-    const int t0 = t_begin + i * TILE;
-    f32x4 S[BPW][RPW];
-#pragma unroll
-    for (int bi = 0; bi < BPW; ++bi) qk_block_swz<RPW>(stg, blk[bi], q, S[bi], lane);
-    const bool full = (t0 + TILE <= t_end) && (t0 + TILE - 1 <= min_pos);
-#pragma unroll
-    for (int bi = 0; bi < BPW; ++bi)
-#pragma unroll
-      for (int rr = 0; rr < RPW; ++rr)
-#pragma unroll
-        for (int ii = 0; ii < 4; ++ii) {
-          float v = S[bi][rr][ii] * a.c2;
-          if (!full) {
-            const int t = t0 + 16 * blk[bi] + 4 * (lane >> 4) + ii;
-            if (t >= t_end || t > rpos[rr]) v = -INFINITY;
-          }
-          S[bi][rr][ii] = v;
-        }
-    softmax_pv_swz<RPW, BPW>(st, stg, blk, S, lane);
-  }
-  const int64_t slot_base_row = ((int64_t)blockIdx.x * TG + tg) * (16 * RT);
-  store_partial<RPW>(st, a.part_o, a.part_ml, slot_base_row, rt0, lane);
-}
-
-// ---------------------------------------------------------------------------- ring variant
 // grid (n_split, Hkv, B), 64 * NWV threads (NWV = 1 or 2 waves), dynamic LDS
 // = NS stages of TW rows of K and V.  The workgroup owns a contiguous token
 // split of one (b, g); each wave owns RT / NWV query row tiles.  The split
@@ -605,8 +502,8 @@ __device__ inline void store_out4(float4 o, float Z, float v_scale, const uint2*
 
 // grid (rows_per_unit, units), 256 threads = 256 / NQ slot groups x NQ =
 // HDIM / 4 column quads.
-// FA: unit = (b, g), row r = c * Gp + h; slots valid = ceil(Lv / split) * TG.
-// SA: unit = (b, g, c), row = h; all n_split * TG slots written.
+// FA: unit = (b, g), row r = c * Gp + h; slots valid = ceil(Lv / split).
+// SA: unit = (b, g, c), row = h; all n_split slots written.
 // ROWS (FA, few partials a row, many rows): grid (ceil(rows_per_unit / SG),
 // units), each slot group merges a row of its own, with no exchange: a
 // workgroup per row is mostly its start (one partial a row: 512 KV heads of 64
@@ -644,8 +541,8 @@ __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
     const LaneLens ll(a.len, a.B, a.max_len);
     const int S = fa_split_len(ll, a.Hkv, a.sp);
     const int Lv = clamp_len(a.len, b, a.max_len);
-    nvalid = ((Lv + S - 1) / S) * a.tg;
-    base = (int64_t)fa_first_item(ll, a.Hkv, S, b, g) * a.tg * a.rows + r;
+    nvalid = (Lv + S - 1) / S;
+    base = (int64_t)fa_first_item(ll, a.Hkv, S, b, g) * a.rows + r;
   }
   if (ROWS && !valid) return;  // (after the wave's shared split search)
   // one pass over the partials: each slot group merges its slots online
@@ -2492,10 +2389,8 @@ __global__ __launch_bounds__(256) void k_stream_probe(const uint4* __restrict__ 
   hipLaunchKernelGGL(kernel, grid, block, shmem, (hipStream_t)(stream), arg)
 
 // Full attention kernel variants (the planner's defaults: head dim 128 with
-// RT = 1 -> 2, RT = 2 -> 5, RT = 4 -> 7, RT = 8 -> 1 (E4M3: 7);
-// head dim 256 with RT = 4, 8 -> 8, else 6):
-//   1: workgroup kernel (64-row stages shared by 4 or 8 waves), head dim 128
-//   0, 2, 3, 5, 7: ring kernels of head dim 128; 6, 8: head dim 256
+// RT = 1 -> 2, RT = 2 -> 5, RT = 4, 8 -> 7; head dim 256 with RT = 4, 8 -> 8,
+// else 6); 0, 2, 3, 5, 7: head dim 128; 6, 8: head dim 256; 1: none
 // Columns: variant, RT, waves per token group, stage rows, stages, token
 // groups, head dim.
 #define HS2_RING_VARIANTS(X)                                                        \
@@ -2512,7 +2407,6 @@ __global__ __launch_bounds__(256) void k_stream_probe(const uint4* __restrict__ 
 constexpr bool fa_ring_ok(int nwv, int tw, bool kv8, int hd) { return tw * (kv8 ? hd : 2 * hd) / 1024 / nwv >= 1; }
 
 int fa_variant_head_dim(int RT, int variant, bool kv8) {
-  if (variant == 1) return !kv8 && (RT == 1 || RT == 2 || RT == 4 || RT == 8) ? 128 : 0;  // workgroup kernel
 #define HS2_RING_HD(v, rt, nwv, tw, ns, tgw, hd) \
   if (variant == v && RT == rt) return fa_ring_ok(nwv, tw, kv8, hd) ? hd : 0;
   HS2_RING_VARIANTS(HS2_RING_HD)
@@ -2526,24 +2420,6 @@ int fa_split_align(int RT, int variant) {
   HS2_RING_VARIANTS(HS2_RING_ALIGN)
 #undef HS2_RING_ALIGN
   return 64;
-}
-
-int fa_ring_token_groups(int RT, int variant) {
-#define HS2_RING_TGW(v, rt, nwv, tw, ns, tgw, hd) \
-  if (variant == v && RT == rt) return tgw;
-  HS2_RING_VARIANTS(HS2_RING_TGW)
-#undef HS2_RING_TGW
-  return 1;
-}
-
-int fa_token_groups(int RT, int variant) {
-  if (variant != 1) return 1;
-  switch (RT) {
-    case 1: return FaShape<1>::TGN;
-    case 2: return FaShape<2>::TGN;
-    case 4: return FaShape<4>::TGN;
-    default: return FaShape<8>::TGN;
-  }
 }
 
 // The runtime's figure, capped so that each resident workgroup's LDS plus
@@ -2625,15 +2501,7 @@ hipError_t fa_wgs_per_cu(int RT, int variant, bool kv8, int* wgs) {
                : fa_ring_occupancy<rt, nwv, tw, ns, tgw, false, hd>(wgs);
   HS2_RING_VARIANTS(HS2_RING_OCC)
 #undef HS2_RING_OCC
-  if (kv8 || variant != 1) return hipSuccess;  // E4M3 only through the ring kernels
-  const size_t sm = (size_t)FA_STAGES * STAGE_BYTES;
-  switch (RT) {
-    case 1: return occupancy_capped(wgs, (const void*)k_fa_split<1>, 64 * FaShape<1>::NW, sm);
-    case 2: return occupancy_capped(wgs, (const void*)k_fa_split<2>, 64 * FaShape<2>::NW, sm);
-    case 4: return occupancy_capped(wgs, (const void*)k_fa_split<4>, 64 * FaShape<4>::NW, sm);
-    case 8: return occupancy_capped(wgs, (const void*)k_fa_split<8>, 64 * FaShape<8>::NW, sm);
-    default: return hipSuccess;
-  }
+  return hipSuccess;
 }
 
 hipError_t launch_fa_split(const FaArgs& a, int RT, int variant, hipStream_t s) {
@@ -2642,16 +2510,7 @@ hipError_t launch_fa_split(const FaArgs& a, int RT, int variant, hipStream_t s) 
   if (variant == v && RT == rt) return fa_ring_dispatch<rt, nwv, tw, ns, tgw, hd>(a, grid, s);
   HS2_RING_VARIANTS(HS2_RING_LAUNCH)
 #undef HS2_RING_LAUNCH
-  if (a.k_scale || variant != 1) return hipErrorInvalidValue;  // E4M3 only through the ring kernels
-  const size_t sm = (size_t)FA_STAGES * STAGE_BYTES;
-  switch (RT) {
-    case 1: HS2_LAUNCH(k_fa_split<1>, grid, dim3(64 * FaShape<1>::NW), sm, s, a); break;
-    case 2: HS2_LAUNCH(k_fa_split<2>, grid, dim3(64 * FaShape<2>::NW), sm, s, a); break;
-    case 4: HS2_LAUNCH(k_fa_split<4>, grid, dim3(64 * FaShape<4>::NW), sm, s, a); break;
-    case 8: HS2_LAUNCH(k_fa_split<8>, grid, dim3(64 * FaShape<8>::NW), sm, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
+  return hipErrorInvalidValue;
 }
 
 template <int RT, int GP, bool KV8, int HDIM>
@@ -2744,10 +2603,6 @@ hipError_t set_pool_smem_limits() {
   if (e == hipSuccess)  // its static LDS is large: only the bitmap's own limit
     e = hipFuncSetAttribute((const void*)k_sel_finish<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)SEL_BM_LDS_MAX);
-  allow((const void*)k_fa_split<1>);
-  allow((const void*)k_fa_split<2>);
-  allow((const void*)k_fa_split<4>);
-  allow((const void*)k_fa_split<8>);
 #define HS2_RING_ATTR(v, rt, nwv, tw, ns, tgw, hd)                                          \
   if (e == hipSuccess) e = fa_ring_allow_lds<rt, nwv, tw, ns, tgw, false, hd>(big);         \
   if (e == hipSuccess) e = fa_ring_allow_lds<rt, nwv, tw, ns, tgw, true, hd>(big);
@@ -2765,7 +2620,7 @@ hipError_t launch_combine(const CombineArgs& a, int rows_per_unit, int64_t units
   // a slot group per row where a row has at most about 8 partials (one per
   // group otherwise) and there are rows enough to fill the chip that way
   const int sg = 256 / (a.hd / 4);
-  const bool rows = !a.sa_mode && a.sp.fixed == 0 && (int64_t)a.sp.n_items * a.tg <= 8 * units &&
+  const bool rows = !a.sa_mode && a.sp.fixed == 0 && a.sp.n_items <= 8 * units &&
                     (int64_t)rows_per_unit * units >= 2048;
   const dim3 grid((unsigned)(rows ? (rows_per_unit + sg - 1) / sg : rows_per_unit), (unsigned)units);
 #define HS2_COMBINE(hdim)                                                      \

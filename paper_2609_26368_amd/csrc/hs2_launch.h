@@ -21,8 +21,8 @@ struct FaArgs {
   const uint16_t* K;
   const uint16_t* V;
   const int32_t* len;
-  float* part_o;   // [n_items * TG][16 RT][HD]
-  float* part_ml;  // [n_items * TG][16 RT][4]: (m ref, l, m true, 0)
+  float* part_o;   // [n_items][16 RT][HD]
+  float* part_ml;  // [n_items][16 RT][4]: (m ref, l, m true, 0)
   int64_t stride_b, stride_h, stride_t;
   float c2;        // softmax scale * log2(e)
   int B, C, Hq, Hkv, G, Gp, max_len;
@@ -60,8 +60,7 @@ struct CombineArgs {
   int B, C, Hq, Hkv, G, Gp, max_len;
   int rows;             // partial rows per slot
   int nslot;            // partial slots per unit
-  int tg;               // slots per split (FA)
-  FaSplitPlan sp;       // FA only: the full-attention pass's splits (partials of item i at slots i * tg ..)
+  FaSplitPlan sp;       // FA only: the full-attention pass's splits (the partial of item i at slot i)
   int sa_mode;
   uint4* clear;         // 16-byte words zeroed by the kernel as a side job, or null
   int64_t n_clear;
@@ -138,10 +137,6 @@ struct SaArgs {
 };
 
 constexpr int kFaVariants = 9;             // full-attention kernel shapes (see HS2_RING_VARIANTS)
-int fa_token_groups(int RT, int variant);  // partial slots per token split
-// token groups that stream contiguous parts of one split through their own
-// rings (ring kernels; merged in LDS into one partial), 1 otherwise
-int fa_ring_token_groups(int RT, int variant);
 int fa_split_align(int RT, int variant);   // split lengths are multiples of this many tokens
 // head dim served by full-attention kernel (RT, variant) for the cache format, 0 if there is none
 int fa_variant_head_dim(int RT, int variant, bool kv8);

@@ -159,20 +159,21 @@ int ilog2(int v) {
   return l;
 }
 
-// Measured on MI355X with one-round splits: 32-token tiles in 3 stages for
-// one row tile; 16-token tiles in 3 stages and two token groups merged in
-// LDS (half the split partials) for two; for four, one row tile per wave
-// (four waves), 32-token tiles in 2 stages and two token groups; for eight,
-// one row tile per wave (eight waves) and 64-token tiles in 2 stages (16
-// queries of 8 heads, 4 x 64K tokens, 4 KV heads: 103 us against 173 for a
-// kernel with four stages and one workgroup per compute unit).  Head dim 256: one row tile per wave, four
-// row tiles in 32-token tiles and 2 stages, fewer in 16-token tiles and 3
-// stages.  The one-row-tile shape serves both cache formats (E4M3 at 512K:
-// 0.624 ms per step against 0.639 with 16-token tiles in 3 stages, whose
-// stored logits also make the score pass slower, 69 against 59 us).
+// Measured on MI355X with one-round splits.  Head dim 128: 32-token tiles in
+// 3 stages for one row tile; from two on one row tile per wave and 2 stages,
+// for two and four in 32-token tiles and two token groups merged in LDS (half
+// the split partials; two row tiles, 3 queries of 6 heads over 5 x 20K tokens:
+// 44 -> 39 us against one wave holding both and 16-token tiles, E4M3 4 x 64K
+// 62 -> 57), for eight in 64-token tiles (16 queries of 8 heads, 4 x 64K
+// tokens, 4 KV heads: 103 us against 173 for a kernel with four stages and
+// one workgroup per compute unit).  Head dim 256: one row tile per wave, four
+// row tiles and more in 32-token tiles and 2 stages, fewer in 16-token tiles
+// and 3 stages.  The one-row-tile shape serves both cache formats (E4M3 at
+// 512K: 0.624 ms per step against 0.639 with 16-token tiles in 3 stages,
+// whose stored logits also make the score pass slower, 69 against 59 us).
 int default_fa_variant(int RT, int hd) {
   if (hd == 256) return RT >= 4 ? 8 : 6;
-  return RT >= 4 ? 7 : RT == 1 ? 2 : 5;
+  return RT == 1 ? 2 : 7;
 }
 
 // kv8: the cache is E4M3 (ring kernels only)
@@ -216,15 +217,11 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   // 346, 345 in two, three, four; 1024 KV heads of up to 3K: 219 -> 181); at
   // head dim 256, whose equal lengths lose up to 3 % below that, only from a
   // KV head per slot on (1024 heads of 3K: 659 -> 584, ragged 407 -> 336).
-  // Two row tiles: about two splits a KV head from 0.6 heads per slot on (512
-  // heads of 5K 255 -> 226, 1024 ragged ones 279 -> 190; 384 heads would
-  // lose, 185 -> 201).  More row tiles lose throughout (64 rows, 512 heads of
-  // 5K: 212 -> 219 -> 236).
+  // More row tiles lose (32 rows, 512 heads of 5K: 202 -> 212; 64 rows: 212
+  // -> 219 -> 236).
   int64_t balance = 1;
   if (p.RT == 1 && (p.D == 128 || p.units > round))
     balance = cdiv(4 * p.units, round);
-  else if (p.RT == 2 && p.D == 128 && 5 * p.units >= 3 * round)
-    balance = cdiv(2 * p.units, round);
   balance = std::min<int64_t>(4, std::max<int64_t>(1, balance));
   const int64_t slots = round * std::max(1, env_int("HS2_FA_ROUNDS", (int)balance));
   const int align = fa_split_align(p.RT, p.fa_variant);

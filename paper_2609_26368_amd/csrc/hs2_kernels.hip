@@ -2389,7 +2389,7 @@ __global__ __launch_bounds__(256) void k_stream_probe(const uint4* __restrict__ 
   hipLaunchKernelGGL(kernel, grid, block, shmem, (hipStream_t)(stream), arg)
 
 // Full attention kernel variants (the planner's defaults: head dim 128 with
-// RT = 1 -> 2, RT = 2 -> 5, RT = 4, 8 -> 7; head dim 256 with RT = 4, 8 -> 8,
+// RT = 1 -> 2, RT = 2, 4, 8 -> 7; head dim 256 with RT = 4, 8 -> 8,
 // else 6); 0, 2, 3, 5, 7: head dim 128; 6, 8: head dim 256; 1: none
 // Columns: variant, RT, waves per token group, stage rows, stages, token
 // groups, head dim.

@@ -71,6 +71,7 @@ struct Plan {
   FaSplitPlan fa_sp;          // full-attention token splits (grid: fa_sp.n_items items)
   int fa_cache_policy;  // FaCachePolicy of the full-attention ring kernel
   int fa_k_keep;        // FA_STREAM_K_HEAD: percent of each token group's K rows kept cacheable
+  bool stream;          // the cache is larger than the last-level cache
   int logit_chunk;
   int pool_split, pool_nsplit;
   int64_t units;              // B * Hkv
@@ -264,6 +265,7 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   {
     const int64_t kv_bytes = 2 * (int64_t)p.B * p.Hkv * p.Lmax * p.D * (kv8 ? 1 : 2);
     const bool stream = kv_bytes > kLastLevelCacheBytes;
+    p.stream = stream;
     // the kernel keeps the last `keep` percent of each token group's part of
     // its split cacheable (a ring kernel with two token groups streams two
     // such parts per split) and streams the K rows before them
@@ -800,6 +802,7 @@ hs2_status sparse_impl(const hs2_dims* dims, const uint16_t* q, const void* K, c
   a.split_slots = sp.split;
   a.n_split = sp.nsplit;
   a.part_rows = 16 * sp.RT;
+  a.stream = p.stream;
   a.out = out;
   a.sink = sink;
   a.gate = gate;

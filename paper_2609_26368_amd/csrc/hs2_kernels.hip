@@ -502,6 +502,12 @@ __device__ inline void store_out4(float4 o, float Z, float v_scale, const uint2*
 
 // grid (rows_per_unit, units), 256 threads = 256 / NQ slot groups x NQ =
 // HDIM / 4 column quads.
+// The O partials, like the stored logits and the scores in the kernels that
+// follow, are read once, non-temporal: left cacheable they take room from
+// what the next pass reads again.  Together (steps or layers, us): 128K chunk
+// of 8 319 -> 304, ragged 16K-128K 250 -> 241, 2 x 512K 1013 -> 992, MQA 64/1
+// chunk of 2 226 -> 221, where the gain falls in the full-attention pass of the
+// next call (185 -> 174, 212 -> 203, 861 -> 842).
 // FA: unit = (b, g), row r = c * Gp + h; slots valid = ceil(Lv / split).
 // SA: unit = (b, g, c), row = h; all n_split slots written.
 // ROWS (FA, few partials a row, many rows): grid (ceil(rows_per_unit / SG),
@@ -554,7 +560,7 @@ __global__ __launch_bounds__(256) void k_combine(CombineArgs a) {
   for (int s = ROWS ? 0 : sg; s < nvalid; s += ROWS ? 1 : SG) {
     const int64_t pr = base + (int64_t)s * a.rows;
     const float4 ml = *(const float4*)(a.part_ml + pr * 4);
-    const float4 o = *(const float4*)(a.part_o + pr * HDIM + 4 * dq);
+    const f32x4 o = __builtin_nontemporal_load((const f32x4*)(a.part_o + pr * HDIM + 4 * dq));
     mt = fmaxf(mt, ml.z);
     const float mn = fmaxf(m, ml.x);
     // an empty partial (m = -inf, O = 0) adds nothing; exp2(-inf) = 0
@@ -862,7 +868,13 @@ __global__ __attribute__((amdgpu_flat_work_group_size(64, 64 * PoolShape<RT, GP,
   auto emit_part = [&](float v, int, int t) { s_part[wave * TW + (t - t0_tile)] = v; };
   auto emit = [&](float v, int c, int t) {
     if (c < a.C && t < nc0 + c) {
-      scores[c * a.score_stride + t] = v;
+      // streamed past the caches like the K rows (uniform): chunk of 8 at 128K
+      // 94.7 -> 89.6 us.  In assembly: the compiler folds the two stores into one
+      // cacheable store.
+      if (a.k_stream)
+        asm volatile("global_store_dword %0, %1, off nt" : : "v"(scores + c * a.score_stride + t), "v"(v) : "memory");
+      else
+        scores[c * a.score_stride + t] = v;
       if (a.hist) {
         const int dg = score_digit(v);
         atomicAdd(&hist[c * (NBINS / 2) + (dg >> 1)], 1u << ((dg & 1) << 4));
@@ -995,7 +1007,7 @@ __global__ __launch_bounds__(NT) void k_pool_logits(PoolArgs a) {
 #pragma unroll 8
       for (int h = 0; h < a.G; ++h) {
         const int r = c * a.G + h;
-        const float4 l = *(const float4*)(lg + r * a.logit_stride + t);
+        const f32x4 l = __builtin_nontemporal_load((const f32x4*)(lg + r * a.logit_stride + t));
         const float f = s_fac[r], m = s_msub[r];
         acc.x += fast_exp2(l.x - m) * f;
         acc.y += fast_exp2(l.y - m) * f;
@@ -1387,7 +1399,7 @@ __device__ inline void load_wave(const float* P, int wt0, int t1, int (&v)[NW]) 
   const int n = t1 - wt0;  // tokens from src on that may be read
   if (n >= 64 * NW) {
 #pragma unroll
-    for (int j = 0; j < NW; ++j) v[j] = src[64 * j + lane];
+    for (int j = 0; j < NW; ++j) v[j] = __builtin_nontemporal_load(src + 64 * j + lane);
   } else {
 #pragma unroll
     for (int j = 0; j < NW; ++j) v[j] = 64 * j + lane < n ? src[64 * j + lane] : 0;
@@ -1731,12 +1743,12 @@ __global__ __launch_bounds__(SELB) void k_score_select(SelArgs a, PoolArgs pa) {
     for (int j = 0; j < NW; ++j) {
       at[j] = min(wt0 + 64 * j + lane, last);  // past the end: a token of the row, not used
       acc[j] = 0.f;
-      cur[j] = lg[at[j]];
+      cur[j] = __builtin_nontemporal_load(lg + at[j]);
     }
     for (int h = 0; h < G; ++h) {
       const float* next = lg + (h + 1 < G ? h + 1 : h) * pa.logit_stride;
 #pragma unroll
-      for (int j = 0; j < NW; ++j) nxt[j] = next[at[j]];
+      for (int j = 0; j < NW; ++j) nxt[j] = __builtin_nontemporal_load(next + at[j]);
       const float m = s_msub[h], f = s_fac[h];
 #pragma unroll
       for (int j = 0; j < NW; ++j) {
@@ -1812,7 +1824,7 @@ __global__ __launch_bounds__(256) void k_block_sums(BlockSelArgs a) {
   for (int u = 0; u < U; ++u) {
     const int t = t0 + 1024 * u + 4 * tid;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[u][i] = t + i < N ? P[t + i] : 0.f;
+    for (int i = 0; i < 4; ++i) v[u][i] = t + i < N ? __builtin_nontemporal_load(P + t + i) : 0.f;
   }
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -2170,7 +2182,7 @@ __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
   __builtin_amdgcn_s_waitcnt(vmcnt_enc(0));
   asm volatile("" ::: "memory");
 
-  auto issue = [&](int tile) __attribute__((always_inline)) {
+  auto issue_as = [&](int tile, auto nt) __attribute__((always_inline)) {
     const uint32_t base = ring + (uint32_t)((tile % NS) * SB);
 #pragma unroll
     for (int u = 0; u < LPM; ++u) {
@@ -2178,9 +2190,19 @@ __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
       const int t = sidx[tile * TW + row];
       const int64_t off = (int64_t)(t < 0 ? 0 : t) * stride_t +
                           16 * ((lane % CPR) ^ (KV8 ? raw_swz<RB>(row) : stage_swz(row)));
-      dma16(Kbg + off, __builtin_amdgcn_readfirstlane(base + 1024 * u));
-      dma16(Vbg + off, __builtin_amdgcn_readfirstlane(base + TW * RB + 1024 * u));
+      dma16_p<decltype(nt)::value>(Kbg + off, __builtin_amdgcn_readfirstlane(base + 1024 * u));
+      dma16_p<decltype(nt)::value>(Vbg + off, __builtin_amdgcn_readfirstlane(base + TW * RB + 1024 * u));
     }
+  };
+  // rows of a cache that the last-level cache cannot hold are read
+  // non-temporal (512 rows of 640 slots 33.9 -> 32.2 us, and the 344 us
+  // full-attention pass of the same step takes 334); one that fits keeps them
+  // (2 rows of 320 slots: 8.8 -> 9.8 us without)
+  auto issue = [&](int tile) __attribute__((always_inline)) {
+    if (a.stream)
+      issue_as(tile, std::true_type{});
+    else
+      issue_as(tile, std::false_type{});
   };
 
   WaveState<1, HDIM> st;

@@ -134,6 +134,7 @@ struct SaArgs {
   const float* sink;     // [Hq] sink logits or null
   const uint16_t* gate;  // [B, C, Hq, D] bf16 output gate logits or null
   const float* v_scale;  // [Hkv] E4M3 cache: output scale of each KV head, or null
+  int stream;            // launch_sa_unit: cache rows are gathered non-temporal
 };
 
 constexpr int kFaVariants = 9;             // full-attention kernel shapes (see HS2_RING_VARIANTS)

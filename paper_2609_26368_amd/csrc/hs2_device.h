@@ -193,8 +193,8 @@ __device__ inline void online_softmax(WaveState<RPW, HDIM>& st, f32x4 (&S)[BPW][
 }
 
 // Write one wave's partial for its RPW row tiles: (m ref, l, m true, 0) and O
-// (rows of HDIM floats).
-template <int RPW, int HDIM>
+// (rows of HDIM floats; NT: non-temporal stores).
+template <bool NT, int RPW, int HDIM>
 __device__ inline void store_partial(const WaveState<RPW, HDIM>& st, float* __restrict__ part_o,
                                      float* __restrict__ part_ml, int64_t slot_base_row, int rt0, int lane) {
 #pragma unroll
@@ -207,7 +207,12 @@ __device__ inline void store_partial(const WaveState<RPW, HDIM>& st, float* __re
     for (int i = 0; i < 4; ++i) {
       float* dst = part_o + (row0 + 4 * (lane >> 4) + i) * HDIM + (lane & 15);
 #pragma unroll
-      for (int nb = 0; nb < WaveState<RPW, HDIM>::NBC; ++nb) dst[16 * nb] = st.o[rr][nb][i];
+      for (int nb = 0; nb < WaveState<RPW, HDIM>::NBC; ++nb) {
+        if constexpr (NT)
+          __builtin_nontemporal_store(st.o[rr][nb][i], dst + 16 * nb);
+        else
+          dst[16 * nb] = st.o[rr][nb][i];
+      }
     }
   }
 }

@@ -405,7 +405,7 @@ __global__ __launch_bounds__(64 * NWV * TGW) void k_fa_ring(FaArgs a) {
   }
   const int64_t slot_base_row = (int64_t)blockIdx.x * (16 * RT);  // one partial per item
   if constexpr (TGW == 1) {
-    store_partial<RPW>(st, a.part_o, a.part_ml, slot_base_row, rt0, lane);
+    store_partial<false>(st, a.part_o, a.part_ml, slot_base_row, rt0, lane);
   } else {
     // merge the token groups in LDS (the rings are free), one partial per split
     constexpr int ROWS = 16 * RT;
@@ -2070,7 +2070,10 @@ __global__ __launch_bounds__(64 * NWV) void k_sa_ring(SaArgs a) {
     }
   }
   const int64_t slot_base_row = (unit * a.n_split + split) * (16 * RT);
-  store_partial<RPW>(st, a.part_o, a.part_ml, slot_base_row, rt0, lane);
+  // several row tiles: their partials (9 MB a layer at MQA 64/1, 8 x 1152
+  // slots) are written past the caches, 11.9 -> 10.5 us; one row tile's are
+  // not (64-head 512K decode: the merge 6.3 -> 6.7)
+  store_partial<(RT > 1)>(st, a.part_o, a.part_ml, slot_base_row, rt0, lane);
 }
 
 // The same layer with one workgroup per (selection row, 16-head tile, split):

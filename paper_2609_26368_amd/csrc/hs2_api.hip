@@ -802,7 +802,10 @@ hs2_status sparse_impl(const hs2_dims* dims, const uint16_t* q, const void* K, c
   a.split_slots = sp.split;
   a.n_split = sp.nsplit;
   a.part_rows = 16 * sp.RT;
-  a.stream = p.stream;
+  // rows of several splits keep their gathers cacheable: a block's next sparse
+  // layer reads them again (128K chunk of 8, 1 + 3 layers: 0.4596 -> 0.4435 ms,
+  // E4M3 0.371 -> 0.349)
+  a.stream = p.stream && sp.nsplit == 1;
   a.out = out;
   a.sink = sink;
   a.gate = gate;

@@ -313,7 +313,7 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   size_t cur = 0;
   // The sa_unit kernel: from 128 workgroups of a 16-head tile of a row on
   // (they keep half the chip's gathers busy by themselves) always, its rows
-  // cut into the fewest splits that its LDS holds; with fewer, only rows that
+  // cut into the fewest splits of at most kSaUnitSlots; with fewer, only rows that
   // one workgroup finishes before the split kernel and its merge would
   // (measured crossings at 2-32 workgroups: 900-1150 slots at head dim 128,
   // 500-650 at 256).  Eight waves while there are not two workgroups per
@@ -325,14 +325,18 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   s.unit_waves = env_int("HS2_SA_SPLIT", 0) > 0 || (wgs < 128 && n_slots > alone) ? 0 : wgs >= 384 ? 4 : 8;
   const int forced = env_int("HS2_SA_UNIT", -1);
   if (forced == 0 || forced == 4 || forced == 8) s.unit_waves = forced;
-  // the workspace is sized for the split kernel, which needs more partials
-  const int split_nsplit = s.nsplit;
-  if (wgs * cdiv(n_slots, kSaUnitSlots) > (1 << 22)) s.unit_waves = 0;  // its grid is one-dimensional
+  const int unit_nsplit = (int)cdiv(n_slots, kSaUnitSlots);
+  if (wgs * unit_nsplit > (1 << 22)) s.unit_waves = 0;  // its grid is one-dimensional
+  // The scratch is the split kernel's, whichever runs: many rows of large
+  // budgets take splits of up to 4096 slots there, and where kSaUnitSlots would
+  // cut them into more (1024 rows of 2560 slots: two against one), the split
+  // kernel keeps them.  (One unit split needs no partials.)
+  const int64_t parts = p.rows * s.nsplit * prow;
+  if (unit_nsplit > s.nsplit) s.unit_waves = 0;
   if (s.unit_waves) {
-    s.nsplit = (int)cdiv(n_slots, kSaUnitSlots);
+    s.nsplit = unit_nsplit;
     s.split = (int)round_up(cdiv(n_slots, s.nsplit), 16);
   }
-  const int64_t parts = p.rows * std::max(s.nsplit, split_nsplit) * prow;
   s.off_part_o = carve(cur, sizeof(float) * parts * p.D);
   s.off_part_ml = carve(cur, sizeof(float) * parts * 4);
   s.bytes = (size_t)round_up((int64_t)cur, kAlign);

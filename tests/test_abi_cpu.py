@@ -276,3 +276,27 @@ def test_noalloc_sparse_rejects_before_launch(lib):
                                      vp(FAKE), None)
     assert st == hs2.HS2_ERR_WORKSPACE
     assert "static scratch" in hs2.hs2_last_error()
+
+
+def test_noalloc_sparse_accepts_what_its_scratch_holds(lib):
+    """The size check passes exactly where the split kernel's partials fit the 16 MiB array, whichever kernel would
+    run: budgets on both sides of what one workgroup of the other kernel holds (2304 slots), rows from few to many.
+    ``out`` is NULL, so the call ends in an error before any launch, with a GPU or without one."""
+    vp = ctypes.c_void_p
+    cdiv = lambda a, b: -(-a // b)  # noqa: E731
+    checked = {True: 0, False: 0}
+    for D in (128, 256):
+        for G in (1, 4, 8, 12, 16, 17, 32, 64):
+            for rows, (B, Hkv, C) in {2: (2, 1, 1), 64: (16, 4, 1), 112: (56, 1, 2), 512: (64, 8, 1),
+                                      1024: (128, 8, 1), 1984: (248, 8, 1), 4000: (500, 8, 1)}.items():
+                for slots in (64, 640, 1152, 2304, 2305, 2560, 3000, 4096, 4097, 4352, 8192, 8704, 20000):
+                    split = min(max(64, cdiv(cdiv(rows * slots, 1024), 64) * 64), cdiv(slots, 64) * 64, 4096)
+                    tiles = 1 << (cdiv(G, 16) - 1).bit_length()
+                    fits = rows * cdiv(slots, split) * 16 * tiles * (D + 4) * 4 <= 16 << 20
+                    d = dims(batch=B, n_queries=C, n_q_heads=G * Hkv, n_kv_heads=Hkv, head_dim=D, max_len=32768)
+                    st = lib.hs2_sparse_attn_noalloc(ctypes.byref(d), vp(FAKE), vp(FAKE), vp(FAKE), vp(FAKE),
+                                                     vp(FAKE), slots, None, None)
+                    assert (st != hs2.HS2_ERR_WORKSPACE) == fits, (D, G, rows, slots, hs2.hs2_last_error())
+                    assert st in (hs2.HS2_ERR_WORKSPACE, hs2.HS2_ERR_HIP, hs2.HS2_ERR_NULL)
+                    checked[fits] += 1
+    assert min(checked.values()) > 100

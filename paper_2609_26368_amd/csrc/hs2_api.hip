@@ -312,30 +312,36 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   const int64_t prow = 16 * s.RT;
   size_t cur = 0;
   // The sa_unit kernel: from 128 workgroups of a 16-head tile of a row on
-  // (they keep half the chip's gathers busy by themselves) always, its rows
-  // cut into the fewest splits of at most kSaUnitSlots; with fewer, only rows that
+  // (they keep half the chip's gathers busy by themselves) always; with fewer, only rows that
   // one workgroup finishes before the split kernel and its merge would
   // (measured crossings at 2-32 workgroups: 900-1150 slots at head dim 128,
-  // 500-650 at 256).  Eight waves while there are not two workgroups per
-  // compute unit, four (two workgroups per unit) from then on.  The rule
-  // takes no device figures and no cache format.  HS2_SA_SPLIT keeps the
-  // split kernel, HS2_SA_UNIT = 0, 4 or 8 chooses.
+  // 500-650 at 256).  HS2_SA_SPLIT keeps the split kernel, HS2_SA_UNIT = 0, 4
+  // or 8 chooses.
+  // Its rows are one split where they can be (no partials, no merge launch):
+  // up to kSaUnitSlots, up to 2304 while there is not a workgroup per compute
+  // unit (128 rows of 4096 slots: two splits 47 us, one 54), up to 3584 from
+  // 384 workgroups on (two of 4 waves then still share a compute unit's LDS:
+  // 384 E4M3 rows of 4096: two splits 79 us, one 94); but never more splits
+  // than the split kernel takes, so the scratch is the same whichever runs:
+  // many rows of large budgets have 4096 slots a split there.
+  // Eight waves while there are not two workgroups per compute unit or where
+  // only one fits, four from then on.
   const int64_t wgs = p.rows * cdiv(p.G, 16);
   const int alone = p.D == 256 ? 512 : 896;
-  s.unit_waves = env_int("HS2_SA_SPLIT", 0) > 0 || (wgs < 128 && n_slots > alone) ? 0 : wgs >= 384 ? 4 : 8;
+  const int64_t one = wgs < 256 ? 2304 : wgs < 384 ? kSaUnitSlots : kSaUnitSlotsPair;
+  const int unit_nsplit = (int)std::max(cdiv(n_slots, kSaUnitSlots), std::min<int64_t>(cdiv(n_slots, one), s.nsplit));
+  const int unit_split = (int)round_up(cdiv(n_slots, unit_nsplit), 16);
+  const bool unit = wgs >= 128 || n_slots <= alone;
+  s.unit_waves = !unit || env_int("HS2_SA_SPLIT", 0) > 0 ? 0
+                 : wgs * unit_nsplit >= 384 && unit_split <= kSaUnitSlotsPair ? 4 : 8;
   const int forced = env_int("HS2_SA_UNIT", -1);
   if (forced == 0 || forced == 4 || forced == 8) s.unit_waves = forced;
-  const int unit_nsplit = (int)cdiv(n_slots, kSaUnitSlots);
   if (wgs * unit_nsplit > (1 << 22)) s.unit_waves = 0;  // its grid is one-dimensional
-  // The scratch is the split kernel's, whichever runs: many rows of large
-  // budgets take splits of up to 4096 slots there, and where kSaUnitSlots would
-  // cut them into more (1024 rows of 2560 slots: two against one), the split
-  // kernel keeps them.  (One unit split needs no partials.)
   const int64_t parts = p.rows * s.nsplit * prow;
-  if (unit_nsplit > s.nsplit) s.unit_waves = 0;
+  if (unit_nsplit > s.nsplit) s.unit_waves = 0;  // (HS2_SA_SPLIT)
   if (s.unit_waves) {
     s.nsplit = unit_nsplit;
-    s.split = (int)round_up(cdiv(n_slots, s.nsplit), 16);
+    s.split = unit_split;
   }
   s.off_part_o = carve(cur, sizeof(float) * parts * p.D);
   s.off_part_ml = carve(cur, sizeof(float) * parts * 4);

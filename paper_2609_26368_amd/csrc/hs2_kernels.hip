@@ -2087,7 +2087,7 @@ __global__ __launch_bounds__(64 * NWV) void k_sa_ring(SaArgs a) {
 // 2 rows of 320 slots 11.0 -> 6.8, 128 rows of 640 16.0 -> 11.3, 256 rows of
 // 1152 39.4 -> 30.3, 512 rows of 640 41.8 -> 33.1; slower where few
 // workgroups hold long rows (4 rows of 2304: 10.0 -> 17.7), which
-// use_sa_unit leaves to the split kernel.
+// make_sa_plan leaves to the split kernel.
 template <int NW, bool KV8, int HDIM>
 struct SaUnit {
   static constexpr int RB = KV8 ? HDIM : 2 * HDIM;  // bytes of a staged row
@@ -2144,9 +2144,12 @@ __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
   int iv[IR];
 #pragma unroll
   for (int k = 0; k < IR; ++k) {
-    const int e = 64 * k + lane;
-    const int slot = (wave + NW * (e / TW)) * TW + e % TW;
-    iv[k] = e < wave_slots && slot < nslots ? irow[slot] : -1;
+    iv[k] = -1;
+    if (64 * k < wave_slots) {  // uniform
+      const int e = 64 * k + lane;
+      const int slot = (wave + NW * (e / TW)) * TW + e % TW;
+      if (e < wave_slots && slot < nslots) iv[k] = irow[slot];
+    }
   }
   uint4 q[1][NKK];
   {

@@ -163,7 +163,8 @@ hipError_t launch_sa_split(const SaArgs& a, int RT, hipStream_t s);
 // sparse layer with one workgroup of NW (4 or 8) waves per (sequence, KV head,
 // query, 16-head tile, split of at most kSaUnitSlots slots); with one split it
 // writes the output, else one partial per split for launch_combine
-constexpr int kSaUnitSlots = 2304;
+constexpr int kSaUnitSlots = 4096;      // as many as a split of the split kernel: never more splits than it needs
+constexpr int kSaUnitSlotsPair = 3584;  // two workgroups of 4 waves with so many slots fit a compute unit's LDS
 hipError_t launch_sa_unit(const SaArgs& a, int NW, hipStream_t s);
 // streaming-read probe over n16 16-byte words (mode: 0 register loads, 1
 // non-temporal register loads, 2 direct-to-LDS loads, 3 non-temporal

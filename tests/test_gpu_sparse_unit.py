@@ -22,6 +22,7 @@ CASES = [  # slots, G, Hkv, D, C, sink and gate
     (1, 8, 2, 128, 1, False), (15, 1, 2, 128, 3, True), (17, 16, 1, 128, 1, False), (65, 17, 1, 128, 2, True),
     (129, 64, 1, 128, 1, False), (640, 5, 4, 128, 1, True), (2304, 8, 1, 128, 1, True), (2305, 8, 1, 128, 1, True),
     (16, 64, 1, 256, 2, True), (129, 3, 2, 256, 1, False), (2304, 8, 1, 256, 1, True), (2400, 16, 1, 256, 1, False),
+    (4096, 1, 8, 128, 16, True), (4097, 1, 8, 128, 16, False),  # 256 rows: the largest split, and one slot more
 ]
 
 
@@ -29,8 +30,8 @@ CASES = [  # slots, G, Hkv, D, C, sink and gate
 @pytest.mark.parametrize("slots,G,Hkv,D,C,extras", CASES, ids=["s%d_g%d_d%d" % (c[0], c[1], c[3]) for c in CASES])
 def test_sparse_unit(slots, G, Hkv, D, C, extras, waves, monkeypatch):
     from paper_2609_26368_amd import hs2
-    B, L = 2, 2500
-    w = W.Workload("unit", B, L, C, G * Hkv, Hkv, D, slots, 0, 1, ctx_min=L // 2)
+    B, L = 2, max(2500, slots + 100)
+    w = W.Workload("unit", B, L, C, G * Hkv, Hkv, D, slots, 0, 1, ctx_min=min(L // 2, 2048))
     inp = W.make_inputs(w, seed=7, kv="fp8")
     note(f"[sparse unit] waves {waves} slots {slots} G {G} Hkv {Hkv} D {D} C {C}")
     rng = np.random.default_rng(slots * 131 + G)

@@ -1,10 +1,13 @@
-"""The one-workgroup-per-row sparse kernel (forced with either wave count) against
-the oracle at the edges of its tiles, waves and splits: one slot, a tile less
+"""The sparse kernels against the oracle, each forced: the one-workgroup-per-row
+kernel with either wave count, and the split kernel with its merge ("0") in
+every shape it is built in (head groups of 1, 2 and 4 tiles, head dim 128 and
+256).  At the edges of their tiles, waves and splits: one slot, a tile less
 and more one, a wave's last tile, the largest split and one slot more; head
 groups below, at and above one 16-head tile; unused and out-of-range slots, an
 empty row, sinks and gates.  The bar is the one of every other sparse layer
-(checker.check_out); a cache in either format that holds the same values has
-to give the same bits, since both take the same tiles in the same order."""
+(checker.check_out); in the one-workgroup kernel a cache in either format that
+holds the same values has to give the same bits, since both take the same
+tiles in the same order."""
 from __future__ import annotations
 
 import numpy as np
@@ -23,10 +26,11 @@ CASES = [  # slots, G, Hkv, D, C, sink and gate
     (129, 64, 1, 128, 1, False), (640, 5, 4, 128, 1, True), (2304, 8, 1, 128, 1, True), (2305, 8, 1, 128, 1, True),
     (16, 64, 1, 256, 2, True), (129, 3, 2, 256, 1, False), (2304, 8, 1, 256, 1, True), (2400, 16, 1, 256, 1, False),
     (4096, 1, 8, 128, 16, True), (4097, 1, 8, 128, 16, False),  # 256 rows: the largest split, and one slot more
+    (300, 32, 1, 128, 1, False), (97, 33, 1, 128, 2, True), (300, 32, 1, 256, 1, True), (97, 33, 1, 256, 1, False),
 ]
 
 
-@pytest.mark.parametrize("waves", ["4", "8"])
+@pytest.mark.parametrize("waves", ["0", "4", "8"])
 @pytest.mark.parametrize("slots,G,Hkv,D,C,extras", CASES, ids=["s%d_g%d_d%d" % (c[0], c[1], c[3]) for c in CASES])
 def test_sparse_unit(slots, G, Hkv, D, C, extras, waves, monkeypatch):
     from paper_2609_26368_amd import hs2
@@ -67,5 +71,7 @@ def test_sparse_unit(slots, G, Hkv, D, C, extras, waves, monkeypatch):
     out8 = blk.sparse(q, K8, V8, lens, didx, kv_scales=sc, **extra)
     out = blk.sparse(q, Kd, Vd, lens, didx, **extra)
     torch.cuda.synchronize()
-    CK.check_out(CK.bf16_bits_to_f64(host_bits(out8)), ref, "sparse unit, E4M3 cache")
-    assert torch.equal(out8.view(torch.int16), out.view(torch.int16)), "the same values in a bf16 cache"
+    CK.check_out(CK.bf16_bits_to_f64(host_bits(out8)), ref, "sparse layer, E4M3 cache")
+    CK.check_out(CK.bf16_bits_to_f64(host_bits(out)), ref, "sparse layer, bf16 cache")
+    if waves != "0":
+        assert torch.equal(out8.view(torch.int16), out.view(torch.int16)), "the same values in a bf16 cache"

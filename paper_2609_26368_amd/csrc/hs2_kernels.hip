@@ -1952,8 +1952,15 @@ __global__ __launch_bounds__(SELB) void k_block_select(BlockSelArgs a) {
 // entries are staged in LDS first; each stage then gathers its rows straight
 // into the ring (per-lane addresses), invalid entries (< 0 or >= len) read
 // row 0 and are masked out of the softmax.
+// Waves per SIMD the registers are budgeted for.  E4M3 rows of head dim 128
+// under several row tiles are bound by the conversions: kept to the 168
+// registers of three waves, the compiler serialises them behind their LDS
+// reads (64 heads, 256 rows, us: 4352 slots 105, with two waves' 256 registers
+// 87; 1152 slots 50 and 46); every other shape is as fast or faster as it comes.
+constexpr int sa_ring_waves_per_simd(int rt, bool kv8, int hd) { return kv8 && hd == 128 && rt > 1 ? 2 : 8; }
 template <int RT, int NWV, int TW, int NS, bool KV8, int HDIM>
-__global__ __launch_bounds__(64 * NWV) void k_sa_ring(SaArgs a) {
+__global__ __launch_bounds__(64 * NWV)
+__attribute__((amdgpu_waves_per_eu(1, sa_ring_waves_per_simd(RT, KV8, HDIM)))) void k_sa_ring(SaArgs a) {
   constexpr int RPW = RT / NWV;
   constexpr int NB = TW / 16;
   constexpr int NKK = HDIM / 32;

@@ -48,6 +48,7 @@
  * (full-attention kernel shape), HS2_FA_SPLIT / HS2_POOL_SPLIT /
  * HS2_SA_SPLIT (tokens or slots per workgroup), HS2_SA_UNIT (sparse layers: 0
  * the split kernel, 4 or 8 the waves of the one-workgroup-per-row kernel),
+ * HS2_SA_STREAM (that kernel's gathers, 0: cacheable, 1: non-temporal),
  * HS2_FA_ROUNDS (workgroup rounds the full-attention splits are sized for), HS2_POOL_FROM_K=1
  * (recompute the scores from K even where the stored logits would serve),
  * HS2_FA_CACHE_POLICY (0: every full-attention load cacheable, 1: V rows

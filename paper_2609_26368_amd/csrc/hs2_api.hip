@@ -812,10 +812,19 @@ hs2_status sparse_impl(const hs2_dims* dims, const uint16_t* q, const void* K, c
   a.split_slots = sp.split;
   a.n_split = sp.nsplit;
   a.part_rows = 16 * sp.RT;
-  // rows of several splits keep their gathers cacheable: a block's next sparse
-  // layer reads them again (128K chunk of 8, 1 + 3 layers: 0.4596 -> 0.4435 ms,
-  // E4M3 0.371 -> 0.349)
-  a.stream = p.stream && sp.nsplit == 1;
+  // Non-temporal gathers (launch_sa_unit) pay where a layer gathers more than
+  // the last-level cache holds, so that the block's next layer would not find
+  // its rows there.  Up to that it does, and the step loses by them; a chunk of
+  // more than four queries shares rows within the layer, as a row's head tiles
+  // do.  Steps of 1 + 3 layers, non-temporal / cacheable, us: 64 sequences of
+  // 1500 tokens, 8 KV heads of 640 slots, 168 MB, 193 / 183; 32 of 16K, 2176
+  // slots, 285 MB, 573 / 558; 64 of 16K, 1152 slots, 302 MB, 1010 / 1010, 2176
+  // slots, 570 MB, 1141 / 1179; chunks of 4, 570 MB, 1416 / 1438; of 8, 570 MB,
+  // 847 / 850, 1107 MB, 1121 / 1098.
+  const int64_t gathered = p.rows * n_slots * 2 * p.D * (kv8 ? 1 : 2);
+  a.stream = p.stream && p.C <= 4 && p.G <= 16 && gathered >= kLastLevelCacheBytes + kLastLevelCacheBytes / 8;
+  const int force_stream = env_int("HS2_SA_STREAM", -1);
+  if (force_stream == 0 || force_stream == 1) a.stream = force_stream;
   a.out = out;
   a.sink = sink;
   a.gate = gate;

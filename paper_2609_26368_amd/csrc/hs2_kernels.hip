@@ -2207,10 +2207,7 @@ __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
       dma16_p<decltype(nt)::value>(Vbg + off, __builtin_amdgcn_readfirstlane(base + TW * RB + 1024 * u));
     }
   };
-  // rows of a cache that the last-level cache cannot hold are read
-  // non-temporal (512 rows of 640 slots 33.9 -> 32.2 us, and the 344 us
-  // full-attention pass of the same step takes 334); one that fits keeps them
-  // (2 rows of 320 slots: 8.8 -> 9.8 us without)
+  // (a.stream: see the plan; 512 rows of 640 slots 33 us cacheable, 30 not)
   auto issue = [&](int tile) __attribute__((always_inline)) {
     if (a.stream)
       issue_as(tile, std::true_type{});

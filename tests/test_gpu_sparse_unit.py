@@ -75,3 +75,9 @@ def test_sparse_unit(slots, G, Hkv, D, C, extras, waves, monkeypatch):
     CK.check_out(CK.bf16_bits_to_f64(host_bits(out)), ref, "sparse layer, bf16 cache")
     if waves != "0":
         assert torch.equal(out8.view(torch.int16), out.view(torch.int16)), "the same values in a bf16 cache"
+    for stream in ("0", "1"):  # the gathers' cache policy changes no result
+        monkeypatch.setenv("HS2_SA_STREAM", stream)
+        for o, k, v, s in ((out8, K8, V8, sc), (out, Kd, Vd, None)):
+            got = blk.sparse(q, k, v, lens, didx, kv_scales=s, **extra)
+            torch.cuda.synchronize()
+            assert torch.equal(got.view(torch.int16), o.view(torch.int16)), f"gather policy {stream}"

@@ -2110,6 +2110,11 @@ struct SaUnit {
   }
   static size_t lds(int split_slots) { return (size_t)RING + sizeof(int32_t) * NW * wave_slots(split_slots); }
 };
+// A row's head tiles and splits are this many workgroups apart.  Several head
+// tiles gather the same rows: a multiple of 8 apart they run on one XCD and
+// share its L2 (64 heads of 2176 slots, us: 90 rows 63, 96 rows 35; what lies
+// past the rows does nothing).
+__host__ __device__ constexpr int sa_unit_apart(int units, int ht) { return ht > 1 ? (units + 7) / 8 * 8 : units; }
 template <int NW, bool KV8, int HDIM>
 __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
   using U = SaUnit<NW, KV8, HDIM>;
@@ -2126,11 +2131,11 @@ __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
 
   const int units = a.B * a.Hkv * a.C;
   const int ht = (a.G + 15) / 16;  // 16-head tiles
-  // a row's head tiles and splits are `units` workgroups apart: with a
-  // multiple of 8 rows they run on one XCD and share its L2
-  const int unit = blockIdx.x % units;
-  const int h0 = 16 * ((blockIdx.x / units) % ht);
-  const int split = blockIdx.x / units / ht;
+  const int apart = sa_unit_apart(units, ht);
+  const int unit = blockIdx.x % apart;
+  if (unit >= units) return;
+  const int h0 = 16 * ((blockIdx.x / apart) % ht);
+  const int split = blockIdx.x / apart / ht;
   const int c = unit % a.C;
   const int g = (unit / a.C) % a.Hkv;
   const int b = unit / (a.C * a.Hkv);
@@ -2741,7 +2746,8 @@ hipError_t launch_sa_split(const SaArgs& a, int RT, hipStream_t s) {
 
 hipError_t launch_sa_unit(const SaArgs& a, int NW, hipStream_t s) {
   if (a.split_slots > kSaUnitSlots) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(a.B * a.Hkv * a.C * ((a.G + 15) / 16) * a.n_split));
+  const int ht = (a.G + 15) / 16;
+  const dim3 grid((unsigned)(sa_unit_apart(a.B * a.Hkv * a.C, ht) * ht * a.n_split));
 #define HS2_SA_UNIT_LAUNCH(nw, hdim)                                                                      \
   if (NW == nw && a.hd == hdim) {                                                                         \
     if (a.k_scale)                                                                                        \

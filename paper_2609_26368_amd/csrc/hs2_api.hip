@@ -312,7 +312,7 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   const int64_t prow = 16 * s.RT;
   size_t cur = 0;
   // The sa_unit kernel: from 128 workgroups of a 16-head tile of a row on
-  // (they keep half the chip's gathers busy by themselves) always; with fewer, only rows that
+  // (they keep half the chip's gathers busy by themselves); with fewer, only rows that
   // one workgroup finishes before the split kernel and its merge would
   // (measured crossings at 2-32 workgroups: 900-1150 slots at head dim 128,
   // 500-650 at 256).  HS2_SA_SPLIT keeps the split kernel, HS2_SA_UNIT = 0, 4
@@ -324,19 +324,37 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   // 384 E4M3 rows of 4096: two splits 79 us, one 94); but never more splits
   // than the split kernel takes, so the scratch is the same whichever runs:
   // many rows of large budgets have 4096 slots a split there.
-  // Eight waves while there are not two workgroups per compute unit or where
-  // only one fits, four from then on.
+  // Eight waves up to a workgroup per compute unit or where only one fits,
+  // four from then on (320 rows of 640 slots: 24 us against 28).
   const int64_t wgs = p.rows * cdiv(p.G, 16);
   const int alone = p.D == 256 ? 512 : 896;
   const int64_t one = wgs < 256 ? 2304 : wgs < 384 ? kSaUnitSlots : kSaUnitSlotsPair;
   const int unit_nsplit = (int)std::max(cdiv(n_slots, kSaUnitSlots), std::min<int64_t>(cdiv(n_slots, one), s.nsplit));
   const int unit_split = (int)round_up(cdiv(n_slots, unit_nsplit), 16);
-  const bool unit = wgs >= 128 || n_slots <= alone;
+  // With more than 16 heads per KV head every 16-head tile gathers the row
+  // again, where the split kernel gathers it once for all.  The tiles' gathers
+  // meet in the caches while they run together and the rows are few: always
+  // up to a workgroup per compute unit; with rows of one split up to two per
+  // unit for 160 MB of rows (120 under two tiles), beyond for rows that the
+  // tiles together gather 280 MB of, and rows short enough that the last round
+  // is not most of the time (64 heads, E4M3, 65 rows: 1152 slots 20 / 20, 2176
+  // 32 / 26, 4096 58 / 32; 128 rows of 2176 36 / 38).  This kernel / the split kernel, us: 64
+  // heads, 64 rows of 2176 slots (256 workgroups) at head dim 128 23 / 29; 128
+  // rows of 1152 at head dim 256 (512, 151 MB) 48 / 58, of 4352 (570 MB) 190 /
+  // 143; 256 rows at head dim 128 (1024) of 320 (42 MB) 26 / 36, 640 (84 MB)
+  // 50 / 47, 1152 90 / 58, 4352 343 / 135.
+  const int64_t ht = cdiv(p.G, 16);
+  const int64_t unit_wgs = wgs * unit_nsplit;
+  const int64_t row_mb = p.rows * n_slots * 2 * p.D * (p.kv8 ? 1 : 2) / 1000000;
+  const bool regather = ht == 1 || unit_wgs <= 256 ||
+                        (unit_nsplit == 1 && n_slots <= 6 * unit_wgs &&
+                         row_mb <= (unit_wgs > 512 ? 280 / ht : ht > 2 ? 160 : 120));
+  const bool unit = wgs >= 128 ? regather : n_slots <= alone;
   s.unit_waves = !unit || env_int("HS2_SA_SPLIT", 0) > 0 ? 0
-                 : wgs * unit_nsplit >= 384 && unit_split <= kSaUnitSlotsPair ? 4 : 8;
+                 : unit_wgs > 256 && unit_split <= kSaUnitSlotsPair ? 4 : 8;
   const int forced = env_int("HS2_SA_UNIT", -1);
   if (forced == 0 || forced == 4 || forced == 8) s.unit_waves = forced;
-  if (wgs * unit_nsplit > (1 << 22)) s.unit_waves = 0;  // its grid is one-dimensional
+  if (unit_wgs > (1 << 22)) s.unit_waves = 0;  // its grid is one-dimensional
   const int64_t parts = p.rows * s.nsplit * prow;
   if (unit_nsplit > s.nsplit) s.unit_waves = 0;  // (HS2_SA_SPLIT)
   if (s.unit_waves) {

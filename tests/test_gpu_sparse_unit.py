@@ -81,3 +81,33 @@ def test_sparse_unit(slots, G, Hkv, D, C, extras, waves, monkeypatch):
             got = blk.sparse(q, k, v, lens, didx, kv_scales=s, **extra)
             torch.cuda.synchronize()
             assert torch.equal(got.view(torch.int16), o.view(torch.int16)), f"gather policy {stream}"
+
+
+ROUTES = [  # B, Hkv, G, D, kv, slots, whether the split kernel and its merge run
+    (32, 8, 64, 128, "bf16", 2176, True), (32, 8, 64, 128, "bf16", 320, False), (16, 8, 64, 128, "bf16", 1152, False),
+    (16, 8, 33, 256, "bf16", 2176, True), (16, 8, 64, 128, "fp8", 2176, False), (32, 8, 64, 128, "fp8", 2176, True),
+    (32, 8, 17, 256, "bf16", 1152, True), (32, 8, 16, 256, "bf16", 1152, False), (8, 8, 64, 128, "bf16", 2176, False),
+]
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,kv,slots,merged", ROUTES, ids=["b%d_g%d_d%d_%s_s%d" % (r[0], *r[2:6]) for r in ROUTES])
+def test_rows_of_many_head_tiles_are_gathered_once(B, Hkv, G, D, kv, slots, merged):
+    """More than 16 heads per KV head over many long rows stay with the kernel that gathers a row once for all
+    heads: head dim 128, 64 heads, 256 rows of 2176 slots take 175 us with a gather per head tile, 82 without."""
+    from paper_2609_26368_amd import hs2
+    note(f"[sparse route] B {B} Hkv {Hkv} G {G} D {D} {kv} slots {slots}")
+    blk = hs2.HybridBlock(B, 1, G * Hkv, Hkv, D, slots, slots, 0)
+    K = torch.randint(0, 64, (B, Hkv, slots, D), device="cuda", dtype=torch.uint8)
+    K = K if kv == "fp8" else K.to(torch.bfloat16)
+    sc = (torch.ones(Hkv, device="cuda"),) * 2 if kv == "fp8" else None
+    q = torch.randn(B, 1, G * Hkv, D, device="cuda").to(torch.bfloat16)
+    idx = torch.arange(slots, dtype=torch.int32, device="cuda").expand(B, Hkv, 1, slots).contiguous()
+    lens = torch.full((B,), slots, dtype=torch.int32, device="cuda")
+    hs2.hs2_timing_enable(True)
+    hs2.hs2_timing_reset()
+    blk.sparse(q, K, K, lens, idx, kv_scales=sc)
+    torch.cuda.synchronize()
+    ran = hs2.hs2_timing_read()
+    hs2.hs2_timing_enable(False)
+    hs2.hs2_timing_reset()
+    assert ("sa_combine" in ran) == merged, ran

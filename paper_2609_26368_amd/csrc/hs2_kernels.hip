@@ -510,7 +510,7 @@ __device__ inline void store_out4(float4 o, float Z, float v_scale, const uint2*
 // next call (185 -> 174, 212 -> 203, 861 -> 842).
 // FA: unit = (b, g), row r = c * Gp + h; slots valid = ceil(Lv / split).
 // SA: unit = (b, g, c), row = h; all n_split slots written.
-// ROWS (FA, few partials a row, many rows): grid (ceil(rows_per_unit / SG),
+// ROWS (FA, few partials a row on average, many rows): grid (ceil(rows_per_unit / SG),
 // units), each slot group merges a row of its own, with no exchange: a
 // workgroup per row is mostly its start (one partial a row: 512 KV heads of 64
 // query rows 58 -> 14 us, 1024 heads 133 -> 26; 512 heads of 4 rows 11.4 -> 8.4).
@@ -2654,11 +2654,18 @@ hipError_t set_pool_smem_limits() {
 }
 
 hipError_t launch_combine(const CombineArgs& a, int rows_per_unit, int64_t units, hipStream_t s) {
-  // a slot group per row where a row has at most about 8 partials (one per
-  // group otherwise) and there are rows enough to fill the chip that way
+  // a slot group per row where rows have about 8 partials on average (one per
+  // group otherwise) and there are rows enough to fill the chip that way.
+  // Every KV head has the same split length, so a long sequence among short
+  // ones has up to its capacity in shortest splits, and one slot group walks
+  // them alone: up to one per 40 rows, as a workgroup per row is slower the more
+  // rows there are (shared / alone, us: 2048 rows 47 of them 16 / 10, 128 12 /
+  // 21; 4096 rows 125 15 / 21; 16384 rows 128 59 / 18)
   const int sg = 256 / (a.hd / 4);
-  const bool rows = !a.sa_mode && a.sp.fixed == 0 && a.sp.n_items <= 8 * units &&
-                    (int64_t)rows_per_unit * units >= 2048;
+  const int64_t all_rows = (int64_t)rows_per_unit * units;
+  const int shortest = a.sp.few_items > units ? a.sp.align : a.sp.min_split;
+  const bool rows = !a.sa_mode && a.sp.fixed == 0 && a.sp.n_items <= 8 * units && all_rows >= 2048 &&
+                    40ll * a.max_len <= all_rows * shortest;
   const dim3 grid((unsigned)(rows ? (rows_per_unit + sg - 1) / sg : rows_per_unit), (unsigned)units);
 #define HS2_COMBINE(hdim)                                                      \
   if (a.hd == hdim) {                                                          \

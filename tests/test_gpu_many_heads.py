@@ -1,9 +1,13 @@
 """Many KV heads at once: the merge with a row per slot group (at least 2048
-rows of at most about 8 partials), and the full-attention splits sized for
-several rounds of workgroups (more than a quarter, or 0.6, of a round's slots
-in KV heads), ragged down to the chunk itself, in both cache formats."""
+rows of about 8 partials on average, their capacity at most a split per 40
+rows), and the full-attention splits sized for several rounds of workgroups
+(more than a quarter, or 0.6, of a round's slots in KV heads), ragged down to
+the chunk itself, in both cache formats; one long sequence among short ones,
+whose rows have about 50 and over a hundred partials, on both sides of that
+capacity."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 
 from paper_2609_26368_amd import workloads as W
@@ -21,3 +25,11 @@ SHAPES = [  # B, Hkv, G, C, D, ctx, kv
 @pytest.mark.parametrize("B,Hkv,G,C,D,ctx,kv", SHAPES, ids=["b%d_kv%d_g%d_c%d_d%d_%s" % (s[:5] + s[6:]) for s in SHAPES])
 def test_many_kv_heads(B, Hkv, G, C, D, ctx, kv):
     parity_case(W.Workload("many_heads", B, ctx, C, G * Hkv, Hkv, D, 40, 20, 1, ctx_min=C), seed=51, kv=kv)
+
+
+@pytest.mark.parametrize("cap", [6500, 6600, 16384])  # 2048 rows: 6553 tokens are 51 shortest splits
+def test_one_long_sequence(cap, monkeypatch):
+    lens = np.full(64, 40, dtype=np.int32)
+    lens[37] = cap
+    monkeypatch.setattr(W, "draw_lengths", lambda w, seed: lens.copy())
+    parity_case(W.Workload("one_long", 64, cap, 2, 16, 1, 128, 40, 20, 1), seed=52)

@@ -172,8 +172,14 @@ int ilog2(int v) {
 // and 3 stages.  The one-row-tile shape serves both cache formats (E4M3 at
 // 512K: 0.624 ms per step against 0.639 with 16-token tiles in 3 stages,
 // whose stored logits also make the score pass slower, 69 against 59 us).
-int default_fa_variant(int RT, int hd) {
+// Two row tiles of an E4M3 cache keep one wave for both tiles (bound by the
+// conversions, which a wave per tile makes twice) where 64 KV heads and more
+// hold 4M tokens together: three workgroups a compute unit balance better than
+// two (256 heads of 8K-32K tokens, us: 277 against 224; 128 of 65000 415
+// against 350); below, the shorter start wins (64 heads of 8K 28 against 31).
+int default_fa_variant(int RT, int hd, bool kv8, int64_t units, int64_t max_len) {
   if (hd == 256) return RT >= 4 ? 8 : 6;
+  if (RT == 2 && kv8 && units >= 64 && units * max_len >= 4000000) return 5;
   return RT == 1 ? 2 : 7;
 }
 
@@ -195,10 +201,11 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   p.c2 = (float)(scale * 1.4426950408889634);
   const int rows16 = (int)cdiv(p.C * p.Gp, 16);
   p.RT = next_pow2(rows16);
-  p.fa_variant = env_int("HS2_FA_VARIANT", default_fa_variant(p.RT, p.D));
-  if (p.fa_variant < 0 || p.fa_variant >= kFaVariants || fa_variant_head_dim(p.RT, p.fa_variant, kv8) != p.D)
-    p.fa_variant = default_fa_variant(p.RT, p.D);
   p.units = (int64_t)p.B * p.Hkv;
+  const int variant = default_fa_variant(p.RT, p.D, kv8, p.units, p.Lmax);
+  p.fa_variant = env_int("HS2_FA_VARIANT", variant);
+  if (p.fa_variant < 0 || p.fa_variant >= kFaVariants || fa_variant_head_dim(p.RT, p.fa_variant, kv8) != p.D)
+    p.fa_variant = variant;
   p.rows = p.units * p.C;
   // token splits: one item (sequence, KV head, split) per workgroup of a
   // grid of as many workgroups as stay resident at once on the device (one

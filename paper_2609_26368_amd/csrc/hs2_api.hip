@@ -239,10 +239,13 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   const int fixed = env_int("HS2_FA_SPLIT", 0);
   if (fixed > 0) {
     p.fa_sp.fixed = (int)std::max<int64_t>(align, round_up(std::min<int64_t>(fixed, p.Lmax), align));
-    p.fa_sp.n_items = (int)(p.units * cdiv(p.Lmax, p.fa_sp.fixed));
+    p.fa_sp.n_items = p.fa_sp.even_items = (int)(p.units * cdiv(p.Lmax, p.fa_sp.fixed));
   } else {
     p.fa_sp.fixed = 0;
-    p.fa_sp.n_items = (int)std::max<int64_t>(slots, p.units);
+    p.fa_sp.even_items = (int)std::max<int64_t>(slots, p.units);
+    // (about as many KV heads as slots: one long sequence among many short ones
+    // would not be cut at all without more items than the grid holds at once)
+    p.fa_sp.n_items = (int)std::max<int64_t>(slots, p.units + round / 4);
   }
   // score pass over K: the same one-round rule for its own kernel; at most
   // 32768 tokens per split (16-bit histogram counters in LDS)

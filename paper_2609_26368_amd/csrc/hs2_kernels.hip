@@ -53,10 +53,9 @@ __device__ inline void load_q_tile(uint4 (&q)[NKK], const uint16_t* __restrict__
 // ---------------------------------------------------------------------------- balanced token splits
 // The full-attention pass cuts each sequence's cache into splits of S tokens
 // and gives every (sequence, KV head, split) item one workgroup of a 1-D
-// grid of sp.n_items workgroups (one residency round).  The lengths live on
-// the device, so every workgroup of the pass and of its merge derives the
-// same S from len[]: the shortest multiple of sp.align, at least
-// sp.min_split, whose items number at most n_items -- ragged lengths then
+// grid of sp.n_items workgroups (one to four residency rounds).  The lengths
+// live on the device, so every workgroup of the pass and of its merge derives
+// the same S from len[], by the rule of FaSplitPlan -- ragged lengths then
 // fill the grid evenly instead of leaving the workgroups past a short
 // sequence's end idle.  sp.fixed > 0 fixes S instead (the grid then covers
 // every split of the capacity).  Items are numbered sequence-major, then KV
@@ -124,43 +123,55 @@ __device__ inline int fa_items_of(const LaneLens& ll, int Hkv, int S) {
   return wave_sum(n) * Hkv;
 }
 
-__device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPlan& sp) {
+// (item: the caller's, if it needs S for one alone: 0 where it has to be none)
+__device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPlan& sp, int item = 0) {
   if (sp.fixed > 0) return sp.fixed;
   float tot = 0.f;
   ll.for_each([&](int, int L) { tot += (float)L; });
   tot = wave_sum(tot) * (float)Hkv;  // token rows over every (sequence, KV head)
   const int units = ll.B * Hkv;
   const float al = (float)sp.align;
+  if (item >= sp.even_items) {  // S < the longest + align below, so these lengths take no more items
+    bool skewed = false;
+    ll.for_each([&](int, int L) { skewed |= (float)(L + sp.align) * (float)units > 4.f * tot; });
+    if (!__any(skewed)) return 0;
+  }
   // items(S) >= tot / S, so S >= tot / n_items; items(S) <= tot / S + units,
   // so S = tot / (n_items - units) fits (with n_items > units), as does any
   // S of at least the capacity (the host makes n_items >= units).  Both ends
   // of the bracket are moved out by more than the float sums' error: items(S)
   // falls as S grows, so the smallest S that fits is the same.
   const int cap_u = (ll.max_len + sp.align - 1) / sp.align;
-  int min_u = (sp.min_split + sp.align - 1) / sp.align;
-  int n_items = sp.n_items;
+  auto shortest = [&](int min_u, int n_items) {
+    const float n = (float)n_items;
+    int lo = max(min_u, (int)(tot * (0.9999f / (n * al))));
+    int hi = cap_u;
+    if (n_items > units) hi = min(cap_u, (int)fminf(tot * (1.0001f / ((n - (float)units) * al)), 1e9f) + 1);
+    hi = max(hi, lo);  // items(lo) <= items(hi) when hi is raised to lo
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    hi = __builtin_amdgcn_readfirstlane(hi);
+    while (lo < hi) {
+      const int mid = (lo + hi) / 2;
+      if (fa_items_of(ll, Hkv, mid * sp.align) <= n_items)
+        hi = mid;
+      else
+        lo = mid + 1;
+    }
+    return hi * sp.align;
+  };
   // so few tokens that splits of min_split would leave compute units idle:
   // the shortest splits of at most one item per unit instead (one 4K
   // sequence of 16 / 2 heads: 64-token splits 7.5 us, 256-token splits 12.5)
-  if (sp.few_items > units && tot <= (float)sp.min_split * (float)sp.few_items) {
-    n_items = sp.few_items;
-    min_u = 1;
-  }
-  const float n = (float)n_items;
-  int lo = max(min_u, (int)(tot * (0.9999f / (n * al))));
-  int hi = cap_u;
-  if (n_items > units) hi = min(cap_u, (int)fminf(tot * (1.0001f / ((n - (float)units) * al)), 1e9f) + 1);
-  hi = max(hi, lo);  // items(lo) <= items(hi) when hi is raised to lo
-  lo = __builtin_amdgcn_readfirstlane(lo);
-  hi = __builtin_amdgcn_readfirstlane(hi);
-  while (lo < hi) {
-    const int mid = (lo + hi) / 2;
-    if (fa_items_of(ll, Hkv, mid * sp.align) <= n_items)
-      hi = mid;
-    else
-      lo = mid + 1;
-  }
-  return hi * sp.align;
+  const bool few = sp.few_items > units && tot <= (float)sp.min_split * (float)sp.few_items;
+  const int min_u = few ? 1 : (sp.min_split + sp.align - 1) / sp.align;
+  int S = shortest(min_u, few ? sp.few_items : sp.even_items);
+  // about as many KV heads as items leave a long sequence among many short
+  // ones uncut (512 heads of 300 tokens, one of 8000, 32 query rows: 120 us, 45
+  // with items for it); lengths that differ less are better off without
+  // them, as items past one round start late (512 heads of 500-9000: 362 us,
+  // 437 with)
+  if (!few && sp.n_items > sp.even_items && (float)S * (float)units > 4.f * tot) S = shortest(min_u, sp.n_items);
+  return S;
 }
 
 // The (sequence, KV head, split) of item `item` with split length S; false
@@ -240,7 +251,8 @@ __global__ __launch_bounds__(64 * NWV * TGW) void k_fa_ring(FaArgs a) {
   const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int tg = wid / NWV, wave = wid % NWV;  // token group, wave in it
   const LaneLens ll(a.len, a.B, a.max_len);
-  const int S = __builtin_amdgcn_readfirstlane(fa_split_len(ll, a.Hkv, a.sp));
+  const int S = __builtin_amdgcn_readfirstlane(fa_split_len(ll, a.Hkv, a.sp, blockIdx.x));
+  if (S == 0) return;
   int b, g, split;
   if (!fa_locate(ll, a.Hkv, S, blockIdx.x, b, g, split)) return;
   // uniform by construction; said so, so that every address derived from

@@ -7,13 +7,14 @@
 namespace hs2 {
 
 // Token splits of the full-attention pass: fixed > 0 fixes the split
-// length; else every workgroup derives the balanced length from len[] (the
+// length; else every workgroup derives the balanced length from len[]: the
 // shortest multiple of align, at least min_split, whose (sequence, KV head,
-// split) items number at most n_items, the grid size; when min_split would
-// give fewer than few_items items, the shortest multiple of align whose items
-// number at most few_items).
+// split) items number at most even_items; where that is over four times the
+// mean length, at most n_items, the grid size; when min_split would give fewer
+// than few_items items, the shortest multiple of align whose items number at
+// most few_items.
 struct FaSplitPlan {
-  int fixed, align, min_split, n_items, few_items;
+  int fixed, align, min_split, even_items, n_items, few_items;
 };
 
 struct FaArgs {

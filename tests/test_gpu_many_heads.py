@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2609_26368_amd import workloads as W
 from tests.test_gpu_parity import parity_case
@@ -33,3 +34,35 @@ def test_one_long_sequence(cap, monkeypatch):
     lens[37] = cap
     monkeypatch.setattr(W, "draw_lengths", lambda w, seed: lens.copy())
     parity_case(W.Workload("one_long", 64, cap, 2, 16, 1, 128, 40, 20, 1), seed=52)
+
+
+def _fa_us(hs2, blk, q, K, V, lens):
+    """Shortest full-attention pass of five calls."""
+    lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    best = float("inf")
+    for _ in range(5):
+        hs2.hs2_timing_enable(True)
+        hs2.hs2_timing_reset()
+        blk.full(q, K, V, lens)
+        torch.cuda.synchronize()
+        best = min(best, 1e3 * hs2.hs2_timing_read()["fa_split"][1])
+        hs2.hs2_timing_enable(False)
+    hs2.hs2_timing_reset()
+    return best
+
+
+@pytest.mark.parametrize("G,C,D", [(16, 2, 128), (64, 1, 128), (64, 1, 256)])
+def test_one_long_sequence_among_as_many_heads_as_slots_is_cut(G, C, D):
+    """512 KV heads fill the grid with an item each; one of 8000 tokens among 300 then has to get more than one. Uncut
+    it takes 4 to 6.5 times the pass of equal lengths of the same sum (120-265 us), cut 1.7 times."""
+    from paper_2609_26368_amd import hs2
+    cap, n = 8000, 512
+    K = torch.randn(n, 1, cap, D, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn(n, C, G, D, device="cuda").to(torch.bfloat16)
+    blk = hs2.HybridBlock(n, C, G, 1, D, cap, 40, 20)
+    long_one = [300] * n
+    long_one[77] = cap
+    even = [sum(long_one) // n] * n
+    t_even, t_long = _fa_us(hs2, blk, q, K, K, even), _fa_us(hs2, blk, q, K, K, long_one)
+    print(f"[one long] G {G} C {C} D {D}: even {t_even:.1f} us, one long {t_long:.1f} us", flush=True)
+    assert t_long < 2.5 * t_even

@@ -234,6 +234,8 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   const int64_t slots = round * std::max(1, env_int("HS2_FA_ROUNDS", (int)balance));
   const int align = fa_split_align(p.RT, p.fa_variant);
   p.fa_sp.align = align;
+  p.fa_sp.avoid = 0;
+  p.fa_sp.longer = 0;
   p.fa_sp.min_split = (int)round_up(256, align);
   p.fa_sp.few_items = (int)std::min<int64_t>(di ? di->cus : 256, round);
   const int fixed = env_int("HS2_FA_SPLIT", 0);
@@ -246,6 +248,16 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
     // (about as many KV heads as slots: one long sequence among many short ones
     // would not be cut at all without more items than the grid holds at once)
     p.fa_sp.n_items = (int)std::max<int64_t>(slots, p.units + round / 4);
+  }
+  // Equal splits of a power of two of a MiB (K and V together) under KV heads
+  // that lie no multiple of a MiB apart meet on the same memory channels: such
+  // splits are made 256 tokens longer (two row tiles, us: 32 heads of 32000
+  // tokens 112 -> 84, 16 of 65000 102 -> 87, E4M3 32 of 65000 125 -> 99; heads a
+  // multiple of a MiB apart do not suffer, 84 -> 86).
+  const int esz = kv8 ? 1 : 2;
+  if (p.RT == 2 && p.fa_variant == 7 && d->kv_stride_h > d->kv_stride_t && (d->kv_stride_h * esz) % (1 << 20)) {
+    p.fa_sp.avoid = (1 << 20) / (2 * p.D * esz);
+    p.fa_sp.longer = 256;
   }
   // score pass over K: the same one-round rule for its own kernel; at most
   // 32768 tokens per split (16-bit histogram counters in LDS)

@@ -171,7 +171,7 @@ __device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPla
   // them, as items past one round start late (512 heads of 500-9000: 362 us,
   // 437 with)
   if (!few && sp.n_items > sp.even_items && (float)S * (float)units > 4.f * tot) S = shortest(min_u, sp.n_items);
-  return S;
+  return S + (sp.avoid > 0 && S % sp.avoid == 0 ? sp.longer : 0);  // (longer splits are no more items)
 }
 
 // The (sequence, KV head, split) of item `item` with split length S; false

@@ -12,9 +12,10 @@ namespace hs2 {
 // split) items number at most even_items; where that is over four times the
 // mean length, at most n_items, the grid size; when min_split would give fewer
 // than few_items items, the shortest multiple of align whose items number at
-// most few_items.
+// most few_items.  A length that is a multiple of avoid > 0 is made `longer`
+// tokens longer.
 struct FaSplitPlan {
-  int fixed, align, min_split, even_items, n_items, few_items;
+  int fixed, align, min_split, even_items, n_items, few_items, avoid, longer;
 };
 
 struct FaArgs {

@@ -66,3 +66,22 @@ def test_one_long_sequence_among_as_many_heads_as_slots_is_cut(G, C, D):
     t_even, t_long = _fa_us(hs2, blk, q, K, K, even), _fa_us(hs2, blk, q, K, K, long_one)
     print(f"[one long] G {G} C {C} D {D}: even {t_even:.1f} us, one long {t_long:.1f} us", flush=True)
     assert t_long < 2.5 * t_even
+
+
+def test_equal_splits_of_a_mebibyte_are_made_longer(monkeypatch):
+    """32 KV heads of 32000 tokens, 32 query rows: the balanced split is 2048 tokens, 1 MiB of K and V, and the heads
+    lie 15.625 MiB apart; the pass takes splits of 2304 then, so its results are those of that fixed length."""
+    from paper_2609_26368_amd import hs2
+    B, Hkv, L = 8, 4, 32000
+    KV = torch.randn(B, Hkv, L, 256, device="cuda", dtype=torch.bfloat16)
+    q = torch.randn(B, 2, 16 * Hkv, 128, device="cuda").to(torch.bfloat16)
+    blk = hs2.HybridBlock(B, 2, 16 * Hkv, Hkv, 128, L, 40, 20, kv_strides=(Hkv * L * 256, L * 256, 256))
+    lens = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    got = []
+    for split in ("0", "2304"):
+        monkeypatch.setenv("HS2_FA_SPLIT", split)
+        stats = torch.empty(B, 2, 16 * Hkv, 2, device="cuda")
+        out, idx = blk.full(q, KV[..., :128], KV[..., 128:], lens, stats=stats)
+        torch.cuda.synchronize()
+        got.append((out.view(torch.int16), idx, stats))
+    assert all(torch.equal(a, b) for a, b in zip(*got))

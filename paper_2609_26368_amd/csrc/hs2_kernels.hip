@@ -1724,8 +1724,18 @@ __global__ __launch_bounds__(SELB) void k_score_select(SelArgs a, PoolArgs pa) {
   const int c = (int)row % a.C;
   const int64_t unit = row / a.C;
   const int G = pa.G;
-  uint32_t* hist = sh.h;  // NBINS of its RDX_BINS words, until the threshold is known
-  hist[tid] = 0;
+  // Histogram: HC copies by lane, two 16-bit counters a word, behind the
+  // candidate list (until the threshold is known).  A row of scores that differ
+  // little has a few bins only, and adds to one address follow one another
+  // (whole call, 16 rows of 16000 tokens, scores within 2 %: one copy 73 us, two
+  // 67, four 64, eight 62, against 65 in two launches; usual scores of 4096
+  // tokens 27.7, 28.0, 27.8, 28.0).
+  constexpr int HC = 4, HSTRIDE = NBINS / 2 + 4;  // copies of a bin in different banks
+  constexpr int HAT = 6144;                       // words of sh.u.comp
+  static_assert(sizeof(CandList<SEL_LDS_CAND>) <= 4 * HAT && 4 * (HAT + HC * HSTRIDE) <= sizeof(sh.u.comp), "");
+  static_assert(SEL_FUSED_TOKENS < 65536 * HC, "16-bit counters");
+  uint32_t* hist = (uint32_t*)sh.u.comp + HAT;
+  for (int i = tid; i < HC * HSTRIDE / 4; i += SELB) ((uint4*)hist)[i] = make_uint4(0, 0, 0, 0);
   if (tid == 0) sh.u.cand.n = 0;
   if (tid < G) {
     const int b = (int)(unit / a.Hkv), g = (int)(unit % a.Hkv);
@@ -1774,7 +1784,8 @@ __global__ __launch_bounds__(SELB) void k_score_select(SelArgs a, PoolArgs pa) {
       if (t < t1) {
         v[j] = __float_as_int(acc[j]);
         if (pa.scores) pa.scores[row * pa.score_stride + t] = acc[j];
-        atomicAdd(&hist[score_digit(acc[j])], 1u);
+        const int dg = score_digit(acc[j]);
+        atomicAdd(&hist[(lane % HC) * HSTRIDE + (dg >> 1)], 1u << (16 * (dg & 1)));
       }
     }
   };
@@ -1787,7 +1798,10 @@ __global__ __launch_bounds__(SELB) void k_score_select(SelArgs a, PoolArgs pa) {
       score(std::integral_constant<int, SEL_PER>{});
   }
   __syncthreads();
-  const int cnt = (int)hist[NBINS - 1 - tid];
+  int cnt = 0;
+#pragma unroll
+  for (int i = 0; i < HC; ++i)
+    cnt += (int)(hist[i * HSTRIDE + (NBINS - 1 - tid) / 2] >> (16 * ((NBINS - 1 - tid) & 1))) & 0xFFFF;
   const Threshold th = find_threshold(cnt, ri, sh);
   const DigitBounds db = digit_bounds(th);
   __syncthreads();  // (find_threshold may return before its barriers)

@@ -29,7 +29,7 @@ def test_score_select_edges(case):
                 seed=41)
 
 
-@pytest.mark.parametrize("L", [70, 4096, 9000])
+@pytest.mark.parametrize("L", [70, 4096, 9000, 16384])
 def test_equal_scores_take_the_lowest_tokens(L):
     """Keys of zero give every candidate the same score: all of them tie at the threshold (more than the LDS list
     holds from 4096 on), and the lowest token indices win."""

@@ -350,7 +350,7 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   // four from then on (320 rows of 640 slots: 24 us against 28).
   const int64_t wgs = p.rows * cdiv(p.G, 16);
   const int alone = p.D == 256 ? 512 : 896;
-  const int64_t one = wgs < 256 ? 2304 : wgs < 384 ? kSaUnitSlots : kSaUnitSlotsPair;
+  const int64_t one = wgs < 256 ? kSaUnitSlotsShort : wgs < 384 ? kSaUnitSlots : kSaUnitSlotsPair;
   const int unit_nsplit = (int)std::max(cdiv(n_slots, kSaUnitSlots), std::min<int64_t>(cdiv(n_slots, one), s.nsplit));
   const int unit_split = (int)round_up(cdiv(n_slots, unit_nsplit), 16);
   // With more than 16 heads per KV head every 16-head tile gathers the row

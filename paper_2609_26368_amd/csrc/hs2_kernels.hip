@@ -171,7 +171,7 @@ __device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPla
   // them, as items past one round start late (512 heads of 500-9000: 362 us,
   // 437 with)
   if (!few && sp.n_items > sp.even_items && (float)S * (float)units > 4.f * tot) S = shortest(min_u, sp.n_items);
-  return S + (sp.avoid > 0 && S % sp.avoid == 0 ? sp.longer : 0);  // (longer splits are no more items)
+  return S + (sp.avoid > 0 && (S & (sp.avoid - 1)) == 0 ? sp.longer : 0);  // (longer splits are no more items)
 }
 
 // The (sequence, KV head, split) of item `item` with split length S; false
@@ -2141,7 +2141,9 @@ struct SaUnit {
 // share its L2 (64 heads of 2176 slots, us: 90 rows 63, 96 rows 35; what lies
 // past the rows does nothing).
 __host__ __device__ constexpr int sa_unit_apart(int units, int ht) { return ht > 1 ? (units + 7) / 8 * 8 : units; }
-template <int NW, bool KV8, int HDIM>
+// SLOTS: most slots of a split (2304, or kSaUnitSlots: every index a lane may
+// hold costs the short rows time, 320 slots 8.8 -> 9.0 us).
+template <int NW, bool KV8, int HDIM, int SLOTS>
 __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
   using U = SaUnit<NW, KV8, HDIM>;
   constexpr int TW = U::TW, NS = U::NS, SB = U::SB, RB = U::RB;
@@ -2177,17 +2179,14 @@ __global__ __launch_bounds__(64 * NW) void k_sa_unit(SaArgs a) {
 
   // everything the layer reads besides the cache is loaded before the first
   // wait: the launch is a chain of memory latencies
-  constexpr int IR = (U::wave_slots(kSaUnitSlots) + 63) / 64;
+  constexpr int IR = (U::wave_slots(SLOTS) + 63) / 64;
   const int32_t* irow = a.idx + (int64_t)unit * a.idx_stride + s_begin;
   int iv[IR];
 #pragma unroll
   for (int k = 0; k < IR; ++k) {
-    iv[k] = -1;
-    if (64 * k < wave_slots) {  // uniform
-      const int e = 64 * k + lane;
-      const int slot = (wave + NW * (e / TW)) * TW + e % TW;
-      if (e < wave_slots && slot < nslots) iv[k] = irow[slot];
-    }
+    const int e = 64 * k + lane;
+    const int slot = (wave + NW * (e / TW)) * TW + e % TW;
+    iv[k] = e < wave_slots && slot < nslots ? irow[slot] : -1;
   }
   uint4 q[1][NKK];
   {
@@ -2659,8 +2658,10 @@ hipError_t set_pool_smem_limits() {
 #undef HS2_POOL_ATTR
   allow((const void*)k_block_select);
 #define HS2_SA_UNIT_ATTR(nw, hd)                      \
-  allow((const void*)k_sa_unit<nw, false, hd>);       \
-  allow((const void*)k_sa_unit<nw, true, hd>);
+  allow((const void*)k_sa_unit<nw, false, hd, kSaUnitSlotsShort>); \
+  allow((const void*)k_sa_unit<nw, true, hd, kSaUnitSlotsShort>);  \
+  allow((const void*)k_sa_unit<nw, false, hd, kSaUnitSlots>);      \
+  allow((const void*)k_sa_unit<nw, true, hd, kSaUnitSlots>);
   HS2_SA_UNIT_SHAPES(HS2_SA_UNIT_ATTR)
 #undef HS2_SA_UNIT_ATTR
   if (e == hipSuccess)  // its static LDS is large: only the bitmap's own limit
@@ -2781,16 +2782,25 @@ hipError_t launch_sa_unit(const SaArgs& a, int NW, hipStream_t s) {
   if (a.split_slots > kSaUnitSlots) return hipErrorInvalidValue;
   const int ht = (a.G + 15) / 16;
   const dim3 grid((unsigned)(sa_unit_apart(a.B * a.Hkv * a.C, ht) * ht * a.n_split));
-#define HS2_SA_UNIT_LAUNCH(nw, hdim)                                                                      \
-  if (NW == nw && a.hd == hdim) {                                                                         \
-    if (a.k_scale)                                                                                        \
-      HS2_LAUNCH((k_sa_unit<nw, true, hdim>), grid, dim3(64 * nw), (SaUnit<nw, true, hdim>::lds(a.split_slots)), s, a);   \
-    else                                                                                                  \
-      HS2_LAUNCH((k_sa_unit<nw, false, hdim>), grid, dim3(64 * nw), (SaUnit<nw, false, hdim>::lds(a.split_slots)), s, a); \
-    return hipGetLastError();                                                                             \
+#define HS2_SA_UNIT_AS(nw, kv8, hdim, slots)                                                                     \
+  HS2_LAUNCH((k_sa_unit<nw, kv8, hdim, slots>), grid, dim3(64 * nw), (SaUnit<nw, kv8, hdim>::lds(a.split_slots)), \
+             s, a)
+#define HS2_SA_UNIT_LAUNCH(nw, hdim)                               \
+  if (NW == nw && a.hd == hdim) {                                  \
+    const bool brief = a.split_slots <= kSaUnitSlotsShort;         \
+    if (a.k_scale && brief)                                        \
+      HS2_SA_UNIT_AS(nw, true, hdim, kSaUnitSlotsShort);           \
+    else if (a.k_scale)                                            \
+      HS2_SA_UNIT_AS(nw, true, hdim, kSaUnitSlots);                \
+    else if (brief)                                                \
+      HS2_SA_UNIT_AS(nw, false, hdim, kSaUnitSlotsShort);          \
+    else                                                           \
+      HS2_SA_UNIT_AS(nw, false, hdim, kSaUnitSlots);               \
+    return hipGetLastError();                                      \
   }
   HS2_SA_UNIT_SHAPES(HS2_SA_UNIT_LAUNCH)
 #undef HS2_SA_UNIT_LAUNCH
+#undef HS2_SA_UNIT_AS
   return hipErrorInvalidValue;
 }
 

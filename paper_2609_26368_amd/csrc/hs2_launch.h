@@ -12,8 +12,8 @@ namespace hs2 {
 // split) items number at most even_items; where that is over four times the
 // mean length, at most n_items, the grid size; when min_split would give fewer
 // than few_items items, the shortest multiple of align whose items number at
-// most few_items.  A length that is a multiple of avoid > 0 is made `longer`
-// tokens longer.
+// most few_items.  A length that is a multiple of avoid (a power of two, or 0:
+// none) is made `longer` tokens longer.
 struct FaSplitPlan {
   int fixed, align, min_split, even_items, n_items, few_items, avoid, longer;
 };
@@ -166,6 +166,7 @@ hipError_t launch_sa_split(const SaArgs& a, int RT, hipStream_t s);
 // query, 16-head tile, split of at most kSaUnitSlots slots); with one split it
 // writes the output, else one partial per split for launch_combine
 constexpr int kSaUnitSlots = 4096;      // as many as a split of the split kernel: never more splits than it needs
+constexpr int kSaUnitSlotsShort = 2304;  // up to here a lane holds fewer indices (see k_sa_unit)
 constexpr int kSaUnitSlotsPair = 3584;  // two workgroups of 4 waves with so many slots fit a compute unit's LDS
 hipError_t launch_sa_unit(const SaArgs& a, int NW, hipStream_t s);
 // streaming-read probe over n16 16-byte words (mode: 0 register loads, 1

@@ -852,17 +852,19 @@ hs2_status sparse_impl(const hs2_dims* dims, const uint16_t* q, const void* K, c
   a.split_slots = sp.split;
   a.n_split = sp.nsplit;
   a.part_rows = 16 * sp.RT;
-  // Non-temporal gathers (launch_sa_unit) pay where a layer gathers more than
-  // the last-level cache holds, so that the block's next layer would not find
-  // its rows there.  Up to that it does, and the step loses by them; a chunk of
-  // more than four queries shares rows within the layer, as a row's head tiles
-  // do.  Steps of 1 + 3 layers, non-temporal / cacheable, us: 64 sequences of
-  // 1500 tokens, 8 KV heads of 640 slots, 168 MB, 193 / 183; 32 of 16K, 2176
-  // slots, 285 MB, 573 / 558; 64 of 16K, 1152 slots, 302 MB, 1010 / 1010, 2176
-  // slots, 570 MB, 1141 / 1179; chunks of 4, 570 MB, 1416 / 1438; of 8, 570 MB,
-  // 847 / 850, 1107 MB, 1121 / 1098.
+  // Non-temporal gathers (launch_sa_unit) pay from a quarter of the last-level
+  // cache on, for a cache that streams past it: what a layer leaves there is
+  // gone before the block's next step, and the passes between do better
+  // without it.  Smaller layers find their rows in the caches again, and so do a
+  // chunk's queries among each other (from more than four on) and a row's head
+  // tiles.  Steps of 1 + 3 layers on three caches in turn, us, non-temporal /
+  // cacheable: 64 sequences of 1K-12K tokens, 8 KV heads of 640 slots, 168 MB,
+  // 434 / 443, E4M3, 84 MB, 306 / 314; of 12K, 2176 slots, 570 MB, 914 / 965;
+  // chunks of 2, 151 MB, 573 / 583; 32 of 4K-16K, 320 slots, 42 MB, 312 / 310,
+  // E4M3, 21 MB, 218 / 215; chunks of 8, 143 MB, 380 / 376; 64 heads per KV head,
+  // 38 MB, 608 / 591.  (One cache step after step: up to 4 % the other way.)
   const int64_t gathered = p.rows * n_slots * 2 * p.D * (kv8 ? 1 : 2);
-  a.stream = p.stream && p.C <= 4 && p.G <= 16 && gathered >= kLastLevelCacheBytes + kLastLevelCacheBytes / 8;
+  a.stream = p.stream && p.C <= 4 && p.G <= 16 && gathered >= kLastLevelCacheBytes / 4;
   const int force_stream = env_int("HS2_SA_STREAM", -1);
   if (force_stream == 0 || force_stream == 1) a.stream = force_stream;
   a.out = out;

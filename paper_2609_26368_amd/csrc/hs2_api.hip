@@ -209,12 +209,13 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   p.rows = p.units * p.C;
   // token splits: one item (sequence, KV head, split) per workgroup of a
   // grid of as many workgroups as stay resident at once on the device (one
-  // round, no tail); the kernels derive the split length from the lengths
-  // on the device (the shortest whose items fill the grid: ragged lengths
-  // balance), a whole number of the kernel's token groups of 64-token tiles
-  // and at least 256 tokens (a split's partial costs 16 RT rows of D + 4
-  // floats).  HS2_FA_SPLIT fixes the length instead (grid: every split of
-  // the capacity).
+  // round, no tail; up to four with one row tile, below); the kernels derive
+  // the split length from the lengths on the device (the shortest whose items
+  // fill the grid: ragged lengths balance), a whole number of the kernel's
+  // token groups of 64-token tiles and at least 256 tokens (a split's partial
+  // costs 16 RT rows of D + 4 floats) unless there are too few of those for
+  // the compute units.  HS2_FA_SPLIT fixes the length instead (grid: every
+  // split of the capacity).
   const int lrt = p.RT >= 8 ? 3 : p.RT >= 4 ? 2 : p.RT >= 2 ? 1 : 0;
   const int wgs_cu = di && di->fa_wgs[kv8][lrt][p.fa_variant] > 0 ? di->fa_wgs[kv8][lrt][p.fa_variant] : 4;
   const int64_t round = (int64_t)(di ? di->cus : 256) * wgs_cu;

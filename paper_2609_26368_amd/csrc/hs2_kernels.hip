@@ -11,11 +11,14 @@
 //                 query heads of the KV head -> pooled score per candidate
 //                 token; builds the first-level radix histogram of the scores
 //   k_pool_logits the same scores from the stored logits (few query rows)
+//   k_score_select  those scores and their selection in one launch (short rows)
 //   k_sel_*       top-k outside the window (radix select on the score keys,
 //                 ties to the lower index) + window union + ascending emission
 //   k_block_*     block-level selection (block score keys, top blocks, emission)
 //   k_sa_ring     sparse attention over gathered selected rows (same partial
-//                 format, merged by k_combine)
+//                 format, merged by k_combine): every head of a row at once
+//   k_sa_unit     the same, one workgroup per row, 16 heads and split: a row of
+//                 one split needs no merge
 //
 // Query rows of one (sequence, KV head) group are laid out query-major:
 // row r = c * Gp + h with Gp = G rounded up to a power of two; rows with
@@ -212,12 +215,12 @@ __device__ inline int fa_first_item(const LaneLens& ll, int Hkv, int S, int b, i
 }
 
 // ============================================================================ full attention
-// grid (n_split, Hkv, B), 64 * NWV threads (NWV = 1 or 2 waves), dynamic LDS
-// = NS stages of TW rows of K and V.  The workgroup owns a contiguous token
-// split of one (b, g); each wave owns RT / NWV query row tiles.  The split
-// streams through a private ring with NS - 1 stages in flight; with one wave
-// there is no barrier at all, with two waves one barrier per stage.  One
-// partial (m, l, O) per split.
+// grid (sp.n_items), 64 * NWV * TGW threads (TGW token groups of NWV waves),
+// dynamic LDS = per token group NS stages of TW rows of K and V.  The
+// workgroup owns a contiguous token split of one (b, g), each token group a
+// part of it and each wave RT / NWV query row tiles.  A part streams through
+// its group's ring with NS - 1 stages in flight; a group of one wave has no
+// barrier, of several one per stage.  One partial (m, l, O) per split.
 // KV8: the cache is E4M3 bytes with one scale per KV head (k_scale folds
 // into the logit scale, v_scale is applied by the merge); each token group
 // stages raw rows in its ring (swizzled by raw_swz).  A one-wave group reads
@@ -2118,9 +2121,10 @@ __attribute__((amdgpu_waves_per_eu(1, sa_ring_waves_per_simd(RT, KV8, HDIM)))) v
 // wave) when there are few rows, by the gather rate when there are many.
 // Against the split kernel and its merge (head dim 128, bf16, us per layer):
 // 2 rows of 320 slots 11.0 -> 6.8, 128 rows of 640 16.0 -> 11.3, 256 rows of
-// 1152 39.4 -> 30.3, 512 rows of 640 41.8 -> 33.1; slower where few
-// workgroups hold long rows (4 rows of 2304: 10.0 -> 17.7), which
-// make_sa_plan leaves to the split kernel.
+// 1152 39.4 -> 30.3, 512 rows of 640 41.8 -> 33.1, 1024 rows of 4096 471 -> 354
+// (non-temporal 316); slower where few workgroups hold long rows (4 rows of
+// 2304: 10.0 -> 17.7) and where several head tiles gather many rows each for
+// itself, which make_sa_plan leaves to the split kernel.
 template <int NW, bool KV8, int HDIM>
 struct SaUnit {
   static constexpr int RB = KV8 ? HDIM : 2 * HDIM;  // bytes of a staged row
@@ -2451,8 +2455,10 @@ __global__ __launch_bounds__(256) void k_stream_probe(const uint4* __restrict__ 
   hipLaunchKernelGGL(kernel, grid, block, shmem, (hipStream_t)(stream), arg)
 
 // Full attention kernel variants (the planner's defaults: head dim 128 with
-// RT = 1 -> 2, RT = 2, 4, 8 -> 7; head dim 256 with RT = 4, 8 -> 8,
-// else 6); 0, 2, 3, 5, 7: head dim 128; 6, 8: head dim 256; 1: none
+// RT = 1 -> 2, RT = 2, 4, 8 -> 7, large E4M3 caches with RT = 2 -> 5; head dim
+// 256 with RT = 4, 8 -> 8, else 6); 0, 2, 3, 5, 7: head dim 128; 6, 8: head dim
+// 256; 1: none.  0, 3 and the other shapes of 2 and 5 run where HS2_FA_VARIANT
+// asks for them.
 // Columns: variant, RT, waves per token group, stage rows, stages, token
 // groups, head dim.
 #define HS2_RING_VARIANTS(X)                                                        \

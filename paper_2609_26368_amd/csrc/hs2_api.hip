@@ -252,13 +252,14 @@ void make_plan(const hs2_dims* d, int32_t k, int32_t window, Plan& p, const Devi
   }
   // Equal splits of a power of two of a MiB (K and V together) under KV heads
   // that lie no multiple of a MiB apart meet on the same memory channels: such
-  // splits are made 256 tokens longer (two row tiles, us: 32 heads of 32000
-  // tokens 112 -> 84, 16 of 65000 102 -> 87, E4M3 32 of 65000 125 -> 99; heads a
-  // multiple of a MiB apart do not suffer, 84 -> 86).
+  // splits are made longer, by 256 tokens, 128 of an E4M3 cache, which is less
+  // bound by memory (two row tiles, us: 32 heads of 32000 tokens 112 -> 84, 16 of
+  // 65000 102 -> 87, E4M3 32 of 65000 125 -> 98, 64 of 32000 96 -> 97, 256 more 101;
+  // heads a multiple of a MiB apart do not suffer, 84 -> 86).
   const int esz = kv8 ? 1 : 2;
   if (p.RT == 2 && p.fa_variant == 7 && d->kv_stride_h > d->kv_stride_t && (d->kv_stride_h * esz) % (1 << 20)) {
     p.fa_sp.avoid = (1 << 20) / (2 * p.D * esz);
-    p.fa_sp.longer = 256;
+    p.fa_sp.longer = kv8 ? 128 : 256;
   }
   // score pass over K: the same one-round rule for its own kernel; at most
   // 32768 tokens per split (16-bit histogram counters in LDS)

@@ -174,7 +174,10 @@ __device__ inline int fa_split_len(const LaneLens& ll, int Hkv, const FaSplitPla
   // them, as items past one round start late (512 heads of 500-9000: 362 us,
   // 437 with)
   if (!few && sp.n_items > sp.even_items && (float)S * (float)units > 4.f * tot) S = shortest(min_u, sp.n_items);
-  return S + (sp.avoid > 0 && (S & (sp.avoid - 1)) == 0 ? sp.longer : 0);  // (longer splits are no more items)
+  // (longer splits are no more items; from 8192 tokens on another align more:
+  // 64 heads of 65000 tokens, us, K and V in one record 338, with 256 tokens more
+  // 362, with 384 336; apart 402, 322, 329)
+  return S + (sp.avoid > 0 && (S & (sp.avoid - 1)) == 0 ? sp.longer + (S >= 8192 ? sp.align : 0) : 0);
 }
 
 // The (sequence, KV head, split) of item `item` with split length S; false

@@ -13,7 +13,7 @@ namespace hs2 {
 // mean length, at most n_items, the grid size; when min_split would give fewer
 // than few_items items, the shortest multiple of align whose items number at
 // most few_items.  A length that is a multiple of avoid (a power of two, or 0:
-// none) is made `longer` tokens longer.
+// none) is made `longer` tokens longer (from 8192 tokens on longer + align).
 struct FaSplitPlan {
   int fixed, align, min_split, even_items, n_items, few_items, avoid, longer;
 };

@@ -359,20 +359,19 @@ void make_sa_plan(const Plan& p, int n_slots, SaPlan& s) {
   // again, where the split kernel gathers it once for all.  The tiles' gathers
   // meet in the caches while they run together and the rows are few: always
   // up to a workgroup per compute unit; with rows of one split up to two per
-  // unit for 160 MB of rows (120 under two tiles), beyond for rows that the
-  // tiles together gather 280 MB of, and rows short enough that the last round
-  // is not most of the time (64 heads, E4M3, 65 rows: 1152 slots 20 / 20, 2176
-  // 32 / 26, 4096 58 / 32; 128 rows of 2176 36 / 38).  This kernel / the split kernel, us: 64
-  // heads, 64 rows of 2176 slots (256 workgroups) at head dim 128 23 / 29; 128
-  // rows of 1152 at head dim 256 (512, 151 MB) 48 / 58, of 4352 (570 MB) 190 /
-  // 143; 256 rows at head dim 128 (1024) of 320 (42 MB) 26 / 36, 640 (84 MB)
-  // 50 / 47, 1152 90 / 58, 4352 343 / 135.
+  // unit for 180 MB of rows, beyond for rows that the tiles together gather
+  // 280 MB of, and rows short enough that the last round is not most of the time
+  // (64 heads, E4M3, 65 rows: 1152 slots 20 / 20, 2176 32 / 26, 4096 58 / 32).  A
+  // layer within steps on three caches in turn, this kernel less the split kernel,
+  // us: 32 heads, 448 workgroups, head dim 128: 640 slots, 73 MB, -10, 1195, 137
+  // MB, -6, 2176, 250 MB, +3; 512 at head dim 256: 640, 168 MB, -12, 1195, 313 MB,
+  // +1, 2176 +18; 64 heads, 1024 workgroups: head dim 128, 320 slots, 42 MB, -7, 640,
+  // 84 MB, +5, 1195 +37, 2176 +84; head dim 256, 2176 +150.
   const int64_t ht = cdiv(p.G, 16);
   const int64_t unit_wgs = wgs * unit_nsplit;
   const int64_t row_mb = p.rows * n_slots * 2 * p.D * (p.kv8 ? 1 : 2) / 1000000;
   const bool regather = ht == 1 || unit_wgs <= 256 ||
-                        (unit_nsplit == 1 && n_slots <= 6 * unit_wgs &&
-                         row_mb <= (unit_wgs > 512 ? 280 / ht : ht > 2 ? 160 : 120));
+                        (unit_nsplit == 1 && n_slots <= 6 * unit_wgs && row_mb <= (unit_wgs > 512 ? 280 / ht : 180));
   const bool unit = wgs >= 128 ? regather : n_slots <= alone;
   s.unit_waves = !unit || env_int("HS2_SA_SPLIT", 0) > 0 ? 0
                  : unit_wgs > 256 && unit_split <= kSaUnitSlotsPair ? 4 : 8;

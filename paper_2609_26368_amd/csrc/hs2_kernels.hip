@@ -2693,15 +2693,25 @@ hipError_t launch_combine(const CombineArgs& a, int rows_per_unit, int64_t units
   // a slot group per row where rows have about 8 partials on average (one per
   // group otherwise) and there are rows enough to fill the chip that way.
   // Every KV head has the same split length, so a long sequence among short
-  // ones has up to its capacity in shortest splits, and one slot group walks
-  // them alone: up to one per 40 rows, as a workgroup per row is slower the more
-  // rows there are (shared / alone, us: 2048 rows 47 of them 16 / 10, 128 12 /
-  // 21; 4096 rows 125 15 / 21; 16384 rows 128 59 / 18)
+  // ones has rows of many partials, and one slot group walks them alone: up to
+  // one per 32 rows, as a workgroup per row is slower the more rows there are
+  // (shared / alone, us, one long sequence: 2048 rows 63 of them 14 / 10, 125 20
+  // / 11; 4096 rows 97 22 / 15; 7168 rows 145 22 / 23; equal lengths: 2048 rows
+  // 7.5 / 10.5; 4096 11 / 18; 7168 11 / 29)
   const int sg = 256 / (a.hd / 4);
   const int64_t all_rows = (int64_t)rows_per_unit * units;
-  const int shortest = a.sp.few_items > units ? a.sp.align : a.sp.min_split;
-  const bool rows = !a.sa_mode && a.sp.fixed == 0 && a.sp.n_items <= 8 * units && all_rows >= 2048 &&
-                    40ll * a.max_len <= all_rows * shortest;
+  // most partials of a row: splits are of min_split at least or, with fewer KV
+  // heads than few_items, shorter and at most few_items; a sequence's KV heads
+  // have as many each, and every other head one
+  const auto most = [&](int split, int64_t items) {
+    return std::min<int64_t>((a.max_len + split - 1) / split, (items - units) / a.Hkv + 1);
+  };
+  bool rows = !a.sa_mode && a.sp.fixed == 0 && a.sp.n_items <= 8 * units && all_rows >= 2048;
+  if (rows) {  // (a sparse layer has no split plan)
+    int64_t parts = most(a.sp.min_split, a.sp.n_items);
+    if (a.sp.few_items > units) parts = std::max(parts, most(a.sp.align, a.sp.few_items));
+    rows = 32 * parts <= all_rows;
+  }
   const dim3 grid((unsigned)(rows ? (rows_per_unit + sg - 1) / sg : rows_per_unit), (unsigned)units);
 #define HS2_COMBINE(hdim)                                                      \
   if (a.hd == hdim) {                                                          \

@@ -28,7 +28,7 @@ def test_many_kv_heads(B, Hkv, G, C, D, ctx, kv):
     parity_case(W.Workload("many_heads", B, ctx, C, G * Hkv, Hkv, D, 40, 20, 1, ctx_min=C), seed=51, kv=kv)
 
 
-@pytest.mark.parametrize("cap", [6500, 6600, 16384])  # 2048 rows: 6553 tokens are 51 shortest splits
+@pytest.mark.parametrize("cap", [6500, 8192, 8193, 16384])  # 2048 rows: 8192 tokens are 64 shortest splits
 def test_one_long_sequence(cap, monkeypatch):
     lens = np.full(64, 40, dtype=np.int32)
     lens[37] = cap
